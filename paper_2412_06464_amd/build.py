@@ -19,10 +19,15 @@ SOURCES = ["gdn_prep.hip", "gdn_seq.hip", "gdn_grad.hip", "gdn_recurrent.hip", "
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++20", "-fPIC",
          # keep the compiler from emitting packed fp32 math
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Extra flags of single sources.  The state passes scale their accumulators
+# with vector instructions in every chunk: results of matrix instructions in
+# vector registers, also where a kernel may use all 512 of a lane (gdn_chain.h;
+# without it, a fourth of the instructions of its loop are moves).
+SOURCE_FLAGS = {"gdn_seq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str, obj: str, extra=()) -> None:
-    cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *SOURCE_FLAGS.get(src, ()), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s%s" % (src, r.stdout, r.stderr))

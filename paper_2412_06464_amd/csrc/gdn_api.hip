@@ -28,6 +28,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 struct Shape {
   int N = 0;      // sequences
   long NC = 0;    // chunks
+  long maxc = 0;  // chunks of the longest sequence
   long Ttot = 0;  // tokens
   size_t esz = 0; // element bytes of q/k/v
 };
@@ -53,14 +54,17 @@ gdn_status check_problem(const gdn_problem* p, Shape* out) {
     long nc = 0;
     for (int n = 0; n < p->num_seqs; ++n) {
       if (cu[n + 1] < cu[n]) return GDN_ERR_CU_SEQLENS;
-      nc += (cu[n + 1] - cu[n] + CH - 1) / CH;
+      const long c = (cu[n + 1] - cu[n] + CH - 1) / CH;
+      nc += c;
+      s.maxc = c > s.maxc ? c : s.maxc;
     }
     s.N = p->num_seqs;
     s.NC = nc;
   } else {
     if (p->cu_seqlens_host) return GDN_ERR_CU_SEQLENS;
     s.N = p->B;
-    s.NC = (long)p->B * ((p->T + CH - 1) / CH);
+    s.maxc = (p->T + CH - 1) / CH;
+    s.NC = (long)p->B * s.maxc;
   }
   if (s.NC >= (1L << 31) / CH) return GDN_ERR_SHAPE;
   *out = s;
@@ -307,6 +311,7 @@ void fill_common(const gdn_problem* p, const Shape& s, Args* a) {
   a->H = p->H;
   a->N = s.N;
   a->NC = (int)s.NC;
+  a->maxc = (int)s.maxc;
   a->T = p->cu_seqlens ? 0 : p->T;
   a->cu = p->cu_seqlens;
 }

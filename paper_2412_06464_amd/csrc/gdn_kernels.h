@@ -13,6 +13,7 @@ struct Args {
   int N;       // sequences (dense: B)
   int NC;      // total chunks over all sequences
   int T;       // dense sequence length (used when cu == nullptr)
+  int maxc;    // chunks of the longest sequence
   int gated;   // 0: alpha == 1 (no log_alpha input): g = 0, no gate math
   const int32_t* cu;  // packed boundaries [N+1] or nullptr (dense)
   // inputs
@@ -26,7 +27,10 @@ struct Args {
   int* seq_chunk0;  // [N+1] first chunk of every sequence
   float* g;         // [ch][64]     cumulative log gate inside the chunk
   // workspace: per-chunk operands of the sequential passes (dtype E), as MFMA
-  // A operands in fragment order with the permuted contraction order
+  // A operands in fragment order with the permuted contraction order.  The
+  // passes of gdn_chain.h read q, k and v themselves: of these they use Wf
+  // (for T diag(b), 64 x 64), Pf, PTf and TTf only, and a fused forward that
+  // is not asked for the rule's q, k and v keeps them in Qf, KbT and Uc.
   void* Wf;   // W~ = T diag(b e^g) K      rows t, k = d     64 x dk
   void* KbT;  // Kbar^T                    rows d, k = t     dk x 64
   void* Uc;   // U~ = T diag(b) V          accumulator layout 64 x dv
@@ -136,6 +140,12 @@ hipError_t launch_prep(Dt dt, int dk, int dv, int mode, const Args& a, hipStream
                        bool block = false);
 hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStream_t s);
 hipError_t launch_bwd_seq(Dt dt, int dk, int dv, const Args& a, hipStream_t s);
+hipError_t launch_fwd_chain(int dk, int dv, int mode, const Args& a, hipStream_t s);
+hipError_t launch_bwd_chain(int dk, int dv, const Args& a, hipStream_t s);
+// Whether a call's state passes are those of gdn_chain.h (bf16 with enough
+// sequence-heads side by side) or those of gdn_seq.hip.  They read different
+// operands, so the prep follows it too.  The same for every call on a problem.
+bool use_chain(Dt dt, int dk, const Args& a);
 hipError_t launch_grad(Dt dt, int dk, int dv, const Args& a, hipStream_t s, bool block = false);
 hipError_t launch_block_fixup(int dk, const Args& a, hipStream_t s);
 hipError_t launch_sum_rows(const float* part, int N, int M, float* tmp, float* out, hipStream_t s);

@@ -112,9 +112,23 @@ Args audit_probe(uint64_t present) {
   return a;
 }
 
-hipError_t launch_fwd(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timing* t,
+// The fused block's forward ahead of the passes of gdn_chain.h: the prep
+// writes the rule's q, k and v (to the caller's buffers, or to the workspace
+// where the caller wants none), the state pass reads them there.
+static Args block_rule_inputs(Args a) {
+  if (!a.yq) a.yq = a.Qf;
+  if (!a.yk) a.yk = a.KbT;
+  if (!a.yv) a.yv = a.Uc;
+  a.q = a.yq;
+  a.k = a.yk;
+  a.v = a.yv;
+  return a;
+}
+
+hipError_t launch_fwd(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timing* t,
                       bool block) {
-  if (audit(block ? Seq::BlockFwd : Seq::Fwd, a) >= 0) return hipErrorInvalidValue;
+  if (audit(block ? Seq::BlockFwd : Seq::Fwd, in) >= 0) return hipErrorInvalidValue;
+  const Args a = block && use_chain(dt, dk, in) ? block_rule_inputs(in) : in;
   hipError_t e;
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
@@ -147,9 +161,10 @@ hipError_t launch_bwd(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timin
 
 // Forward that keeps what the backward needs: the prep writes both operand
 // sets and the state pass stores chunk states and V' beside O.
-hipError_t launch_fwd_save(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timing* t,
+hipError_t launch_fwd_save(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timing* t,
                            bool block) {
-  if (audit(block ? Seq::BlockFwdSave : Seq::FwdSave, a) >= 0) return hipErrorInvalidValue;
+  if (audit(block ? Seq::BlockFwdSave : Seq::FwdSave, in) >= 0) return hipErrorInvalidValue;
+  const Args a = block && use_chain(dt, dk, in) ? block_rule_inputs(in) : in;
   hipError_t e;
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=

@@ -99,7 +99,11 @@ __device__ inline void export_afrag_perm_pair(E* dst_raw, E* dst_scaled, const E
 // normalisation of q and k) runs in place of the row loads: the rule's q, k
 // and v are formed in registers from the projections a.xq, a.xk, a.xv (and
 // written to a.yq, a.yk, a.yv where those are set).
-template <class E, int DK, int DV, int MODE, bool BLK = false>
+// SMALL: ahead of the passes of gdn_chain.h, which read q, k and v
+// themselves: only the 64 x 64 matrices are formed (T diag(b) and P, and for
+// the backward P^T, T^T and Ak^T; no v, and with BLK the rule's q, k and v
+// written out).
+template <class E, int DK, int DV, int MODE, bool BLK = false, bool SMALL = false>
 __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   using M = Mfma<E>;
   // operands of the forward pass (diag(e^g) Q, P), of the reverse pass and
@@ -134,7 +138,8 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   // t, 16-byte vectors cv = w + 4 i of each 64-wide column slice.
   constexpr int EPV = 16 / sizeof(E), NI = 64 / EPV / 4;
   constexpr int KS = DK / 64, VS = DV / 64;
-  uint4 rk[KS][NI], rq[KS][NI], rv[VS][NI];
+  constexpr int VR = SMALL && !BLK ? 0 : VS;  // slices of v
+  uint4 rk[KS][NI], rq[KS][NI], rv[VR > 0 ? VR : 1][NI];
   if constexpr (!BLK) {
     const int t = lane_id();
     const bool tv = t < len;
@@ -148,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
         rq[sl][i] = tv ? *reinterpret_cast<const uint4*>(Q + ko + c) : uint4{0u, 0u, 0u, 0u};
       }
 #pragma unroll
-    for (int sl = 0; sl < VS; ++sl)
+    for (int sl = 0; sl < VR; ++sl)
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const int c = 64 * sl + (w + 4 * i) * EPV;
@@ -320,12 +325,12 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     lds_barrier();
     wave_mma_nt<E, 1, 4, 64>(kk, sX + w * 16 * LD, LD, sX, LD);
     wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
-    if (FOUT) {
+    if (FOUT && !SMALL) {
       // diag(e^g) Q as A operands (rows t, k = d) for the output of the forward pass
       export_afrag_perm_kslice<E, CH, DK, 64, 256>(
           (E*)a.Qf + ch * CH * DK, 64 * s, [&](int t, int d) { return seg[t] * to_f(sY[t * LD + d]); });
     }
-    if (BOUT) {
+    if (BOUT && !SMALL) {
       // raw K as A operands (rows t, k = d) for K dS in the reverse pass
       export_afrag_perm_kslice<E, CH, DK, 64, 256>(
           (E*)a.Kf + ch * CH * DK, 64 * s, [&](int t, int d) { return to_f(sX[t * LD + d]); });
@@ -410,11 +415,21 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     for (int e = 0; e < 4; ++e) sTf[(32 + 16 * I + 4 * lg + e) * LDA + 16 * J + lr] = -z[e];
   }
   lds_barrier();
-  for (int idx = tid; idx < CH * CH; idx += 256) {
-    const int r = idx >> 6, i = idx & 63;
-    sT[r * LD + i] = to_e<E>(((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]);
+  // T (zero above the diagonal blocks, where the buffer holds none)
+  auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
+  if constexpr (SMALL) {
+    export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
+                                      [&](int t, int i) { return T_at(t, i) * sb[i]; });
+    if (BOUT)
+      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                        [&](int i, int t) { return T_at(t, i); });
+  } else {
+    for (int idx = tid; idx < CH * CH; idx += 256) {
+      const int r = idx >> 6, i = idx & 63;
+      sT[r * LD + i] = to_e<E>(T_at(r, i));
+    }
+    lds_barrier();
   }
-  lds_barrier();
 
   // ---- 64 x 64 operands
   if (FOUT) {
@@ -424,12 +439,14 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   if (BOUT) {
     export_afrag_perm<E, CH, CH, 256>((E*)a.PTf + ch * CH * CH,
                                       [&](int i, int t) { return to_f(sP[t * LD + i]); });
-    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
-                                      [&](int i, int t) { return to_f(sT[t * LD + i]); });
+    if (!SMALL)
+      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                        [&](int i, int t) { return to_f(sT[t * LD + i]); });
   }
+  if constexpr (SMALL) return;
 
   // ---- dk slices: W~ (and -W~^T), Kbar^T, (e^g Q)^T
-  static_for<0, KS>([&](auto sc) {
+  static_for<0, SMALL ? 0 : KS>([&](auto sc) {
     constexpr int s = decltype(sc)::value;
     put_T(sX, rk[s], 1.f);  // sX[d][t]
     if (BOUT) put_T(sY, rq[s], 1.f);
@@ -484,7 +501,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
 
   // ---- dv slices: U~ = T (b V), accumulator layout
   const float bt = sb[lane_id()];
-  static_for<0, VS>([&](auto sc) {
+  static_for<0, SMALL ? 0 : VS>([&](auto sc) {
     constexpr int s = decltype(sc)::value;
     put_T(sX, rv[s], bt);  // sX[v][t] = b_t V
     lds_barrier();
@@ -512,26 +529,28 @@ hipError_t launch_prep(Dt dt, int dk, int dv, int mode, const Args& a, hipStream
     return hipErrorInvalidValue;
   if (block && mode == PREP_SAVE && (!a.yq || !a.yk || !a.yv))
     return hipErrorInvalidValue;  // the backward reads the rule's q, k, v
+  const bool small = use_chain(dt, dk, a);
+  const dim3 grid(a.NC, a.H);
   auto f = [&]<class E, int DK, int DV>() {
+    auto go = [&]<int MODE, bool BLK>() {
+      if constexpr (sizeof(E) == 2) {
+        if (small) {
+          hipLaunchKernelGGL((k_prep<E, DK, DV, MODE, BLK, true>), grid, dim3(256), 0, s, a);
+          return hipGetLastError();
+        }
+      }
+      hipLaunchKernelGGL((k_prep<E, DK, DV, MODE, BLK, false>), grid, dim3(256), 0, s, a);
+      return hipGetLastError();
+    };
     if (block) {  // fused block prologue (bf16): forward and saving forward only
       if constexpr (sizeof(E) != 2) return hipErrorInvalidValue;
-      else if (mode == PREP_SAVE)
-        hipLaunchKernelGGL((k_prep<E, DK, DV, PREP_SAVE, true>), dim3(a.NC, a.H), dim3(256), 0, s,
-                           a);
-      else if (mode == PREP_FWD)
-        hipLaunchKernelGGL((k_prep<E, DK, DV, PREP_FWD, true>), dim3(a.NC, a.H), dim3(256), 0, s,
-                           a);
-      else
-        return hipErrorInvalidValue;
-      return hipGetLastError();
+      else if (mode == PREP_SAVE) return go.template operator()<PREP_SAVE, true>();
+      else if (mode == PREP_FWD) return go.template operator()<PREP_FWD, true>();
+      else return hipErrorInvalidValue;
     }
-    if (mode == PREP_BWD)
-      hipLaunchKernelGGL((k_prep<E, DK, DV, PREP_BWD>), dim3(a.NC, a.H), dim3(256), 0, s, a);
-    else if (mode == PREP_SAVE)
-      hipLaunchKernelGGL((k_prep<E, DK, DV, PREP_SAVE>), dim3(a.NC, a.H), dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_prep<E, DK, DV, PREP_FWD>), dim3(a.NC, a.H), dim3(256), 0, s, a);
-    return hipGetLastError();
+    if (mode == PREP_BWD) return go.template operator()<PREP_BWD, false>();
+    if (mode == PREP_SAVE) return go.template operator()<PREP_SAVE, false>();
+    return go.template operator()<PREP_FWD, false>();
   };
   GDN_DISPATCH(dt, dk, dv, f);
 }

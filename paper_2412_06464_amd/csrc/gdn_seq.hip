@@ -1,5 +1,6 @@
 // Sequential inter-chunk state passes (gfx950) of the chunkwise gated delta
-// rule (Sec. 3.3; state stored dk x dv).  One workgroup owns one (sequence,
+// rule (Sec. 3.3; state stored dk x dv): in fp32, and in bf16 where few
+// sequence-heads run side by side (the others: gdn_chain.h, and the rule there).  One workgroup owns one (sequence,
 // head, BV-wide slice of dv): the dk x BV state tile lives in the MFMA
 // accumulators of its four waves (wave w owns state rows [w dk/4, (w+1) dk/4))
 // and the chunks of the sequence are walked in order.  Per chunk the state
@@ -18,6 +19,8 @@
 #include "gdn_device.h"
 #include "gdn_kernels.h"
 #include "gdn_seq_common.h"
+
+#include "gdn_chain.h"
 
 namespace gdn {
 
@@ -663,6 +666,7 @@ __global__ __launch_bounds__(256, GDN_SEQ_MINB) void k_bwd_seq(Args a) {
 // ------------------------------------------------------------------ launchers
 
 hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStream_t s) {
+  if (use_chain(dt, dk, a)) return launch_fwd_chain(dk, dv, mode, a, s);
   auto f = [&]<class E, int DK, int DV>() {
     constexpr int BV = SeqCfg<E, DK, DV>::BV, FBV = SeqCfg<E, DK, DV>::FWD_BV;
     constexpr int SBV = SeqCfg<E, DK, DV>::SAVE_BV;
@@ -681,6 +685,7 @@ hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStr
 }
 
 hipError_t launch_bwd_seq(Dt dt, int dk, int dv, const Args& a, hipStream_t s) {
+  if (use_chain(dt, dk, a)) return launch_bwd_chain(dk, dv, a, s);
   auto f = [&]<class E, int DK, int DV>() {
     constexpr int BV = SeqCfg<E, DK, DV>::BV;
     const dim3 grid(unit_tile_grid(DV / BV, a.N * a.H));
