@@ -92,6 +92,70 @@ __device__ inline void export_afrag_perm_pair(E* dst_raw, E* dst_scaled, const E
     store_stream_small(dst_scaled + (size_t)u * M::KPL, xs.f);
   }
 }
+// T = (I + A)^-1 of a strictly lower 64 x 64 A in LDS (both fp32, leading
+// dimension LDA), by block recursion, over 256 threads; on return every thread
+// sees T.  The 16x16 diagonal blocks by forward substitution (one column per
+// thread); then, with fp32 MFMA, the off-diagonal block of each 32x32 diagonal
+// block and finally the lower-left 32x32 block, each as
+//   T_21 = -T_22 (A_21 T_11)
+// for a block lower-triangular [[T_11, 0], [T_21, T_22]].  sYb: 32 * 33 floats
+// of scratch.  The 16x16 blocks right of the diagonal blocks are not written.
+template <int LDA>
+__device__ inline void invert_unit_lower(const float* sA, float* sTf, float* sYb) {
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
+  if (tid < CH) {
+    const int blk = tid >> 4, j = tid & 15, o = blk * 16;
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float s = (i == j) ? 1.f : 0.f;
+#pragma unroll
+      for (int l = 0; l < i; ++l) s -= sA[(o + i) * LDA + o + l] * x[l];
+      x[i] = s;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sTf[(o + i) * LDA + o + j] = x[i];
+  }
+  lds_barrier();
+  {
+    using MF = Mfma<float>;
+    const int lr = lane_id() & 15, lg = lane_id() >> 4;
+    // 16 x 16 x 16 product tile: acc += X[xr.., xc..] Y[yr.., yc..] (fp32 LDS, leading dims)
+    auto mm16 = [&](f32x4& acc, const float* X, int ldx, int xr, int xc, const float* Y, int ldy,
+                    int yr, int yc) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        acc = MF::mma(X[(xr + lr) * ldx + xc + 4 * ks + lg], Y[(yr + 4 * ks + lg) * ldy + yc + lr], acc);
+    };
+    // 32x32 diagonal blocks (waves 0 and 1): T[o+16.., o..] = -T[o+16.., o+16..] (A[o+16.., o..] T[o.., o..])
+    if (w < 2) {
+      const int o = 32 * w;
+      float* yb = sYb + w * 16 * 17;
+      f32x4 y = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
+      mm16(y, sA, LDA, o + 16, o, sTf, LDA, o, o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) yb[(4 * lg + e) * 17 + lr] = y[e];  // read back by this wave only
+      mm16(z, sTf, LDA, o + 16, o + 16, yb, 17, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sTf[(o + 16 + 4 * lg + e) * LDA + o + lr] = -z[e];
+    }
+    lds_barrier();
+    // lower-left 32x32 block, one 16x16 tile (I, J) per wave:
+    //   Y = A[32.., 0..32] T[0..32, 0..32]  (T lower: k-blocks K >= J)
+    //   T[32 + 16 I.., 16 J..] = -sum_{K <= I} T[32 + 16 I.., 32 + 16 K..] Y[16 K.., 16 J..]
+    const int I = w >> 1, J = w & 1;
+    f32x4 y = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
+    for (int K = J; K < 2; ++K) mm16(y, sA, LDA, 32 + 16 * I, 16 * K, sTf, LDA, 16 * K, 16 * J);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sYb[(16 * I + 4 * lg + e) * 33 + 16 * J + lr] = y[e];
+    lds_barrier();
+    for (int K = 0; K <= I; ++K) mm16(z, sTf, LDA, 32 + 16 * I, 32 + 16 * K, sYb, 33, 16 * K, 16 * J);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sTf[(32 + 16 * I + 4 * lg + e) * LDA + 16 * J + lr] = -z[e];
+  }
+  lds_barrier();
+}
+
 // Grid (NC, H), 256 threads (4 waves).  LDS stays below 80 KB for bf16 so
 // that two workgroups share a CU: one streams while the other solves.
 
@@ -99,12 +163,13 @@ __device__ inline void export_afrag_perm_pair(E* dst_raw, E* dst_scaled, const E
 // normalisation of q and k) runs in place of the row loads: the rule's q, k
 // and v are formed in registers from the projections a.xq, a.xk, a.xv (and
 // written to a.yq, a.yk, a.yv where those are set).
-// SMALL: ahead of the passes of gdn_chain.h, which read q, k and v
-// themselves: only the 64 x 64 matrices are formed (T diag(b) and P, and for
-// the backward P^T, T^T and Ak^T; no v, and with BLK the rule's q, k and v
-// written out).
+// SMALL (with BLK only; k_prep_small is the one without): ahead of the passes
+// of gdn_chain.h, which read q, k and v themselves: beside the rule's q, k and
+// v only the 64 x 64 matrices are written (T diag(b) and P, and for the
+// backward P^T, T^T and Ak^T).
 template <class E, int DK, int DV, int MODE, bool BLK = false, bool SMALL = false>
 __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
+  static_assert(BLK || !SMALL, "k_prep_small");
   using M = Mfma<E>;
   // operands of the forward pass (diag(e^g) Q, P), of the reverse pass and
   // gradient kernel (K, P^T, T^T, -W~^T, (e^g Q)^T, Ak^T), or both
@@ -138,8 +203,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   // t, 16-byte vectors cv = w + 4 i of each 64-wide column slice.
   constexpr int EPV = 16 / sizeof(E), NI = 64 / EPV / 4;
   constexpr int KS = DK / 64, VS = DV / 64;
-  constexpr int VR = SMALL && !BLK ? 0 : VS;  // slices of v
-  uint4 rk[KS][NI], rq[KS][NI], rv[VR > 0 ? VR : 1][NI];
+  uint4 rk[KS][NI], rq[KS][NI], rv[VS][NI];
   if constexpr (!BLK) {
     const int t = lane_id();
     const bool tv = t < len;
@@ -153,7 +217,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
         rq[sl][i] = tv ? *reinterpret_cast<const uint4*>(Q + ko + c) : uint4{0u, 0u, 0u, 0u};
       }
 #pragma unroll
-    for (int sl = 0; sl < VR; ++sl)
+    for (int sl = 0; sl < VS; ++sl)
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const int c = 64 * sl + (w + 4 * i) * EPV;
@@ -358,63 +422,8 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   }
   lds_barrier();
 
-  // ---- T = (I + A)^-1, A strictly lower, by block recursion.  The 16x16
-  // diagonal blocks by forward substitution (one column per thread); then,
-  // with fp32 MFMA, the off-diagonal block of each 32x32 diagonal block and
-  // finally the lower-left 32x32 block, each as
-  //   T_21 = -T_22 (A_21 T_11)
-  // for a block lower-triangular [[T_11, 0], [T_21, T_22]].
-  if (tid < CH) {
-    const int blk = tid >> 4, j = tid & 15, o = blk * 16;
-    float x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float s = (i == j) ? 1.f : 0.f;
-#pragma unroll
-      for (int l = 0; l < i; ++l) s -= sA[(o + i) * LDA + o + l] * x[l];
-      x[i] = s;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sTf[(o + i) * LDA + o + j] = x[i];
-  }
-  lds_barrier();
-  {
-    using MF = Mfma<float>;
-    const int lr = lane_id() & 15, lg = lane_id() >> 4;
-    // 16 x 16 x 16 product tile: acc += X[xr.., xc..] Y[yr.., yc..] (fp32 LDS, leading dims)
-    auto mm16 = [&](f32x4& acc, const float* X, int ldx, int xr, int xc, const float* Y, int ldy,
-                    int yr, int yc) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        acc = MF::mma(X[(xr + lr) * ldx + xc + 4 * ks + lg], Y[(yr + 4 * ks + lg) * ldy + yc + lr], acc);
-    };
-    // 32x32 diagonal blocks (waves 0 and 1): T[o+16.., o..] = -T[o+16.., o+16..] (A[o+16.., o..] T[o.., o..])
-    if (w < 2) {
-      const int o = 32 * w;
-      float* yb = sYb + w * 16 * 17;
-      f32x4 y = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
-      mm16(y, sA, LDA, o + 16, o, sTf, LDA, o, o);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) yb[(4 * lg + e) * 17 + lr] = y[e];  // read back by this wave only
-      mm16(z, sTf, LDA, o + 16, o + 16, yb, 17, 0, 0);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sTf[(o + 16 + 4 * lg + e) * LDA + o + lr] = -z[e];
-    }
-    lds_barrier();
-    // lower-left 32x32 block, one 16x16 tile (I, J) per wave:
-    //   Y = A[32.., 0..32] T[0..32, 0..32]  (T lower: k-blocks K >= J)
-    //   T[32 + 16 I.., 16 J..] = -sum_{K <= I} T[32 + 16 I.., 32 + 16 K..] Y[16 K.., 16 J..]
-    const int I = w >> 1, J = w & 1;
-    f32x4 y = {0.f, 0.f, 0.f, 0.f}, z = {0.f, 0.f, 0.f, 0.f};
-    for (int K = J; K < 2; ++K) mm16(y, sA, LDA, 32 + 16 * I, 16 * K, sTf, LDA, 16 * K, 16 * J);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) sYb[(16 * I + 4 * lg + e) * 33 + 16 * J + lr] = y[e];
-    lds_barrier();
-    for (int K = 0; K <= I; ++K) mm16(z, sTf, LDA, 32 + 16 * I, 32 + 16 * K, sYb, 33, 16 * K, 16 * J);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) sTf[(32 + 16 * I + 4 * lg + e) * LDA + 16 * J + lr] = -z[e];
-  }
-  lds_barrier();
+  // ---- T = (I + A)^-1
+  invert_unit_lower<LDA>(sA, sTf, sYb);
   // T (zero above the diagonal blocks, where the buffer holds none)
   auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
   if constexpr (SMALL) {
@@ -515,6 +524,110 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   });
 }
 
+// The prep ahead of the passes of gdn_chain.h: g, T and P only (SMALL in
+// k_prep; with the block prologue that kernel does it).  Bound by the latency
+// of its phases (loads, Gram products, the inverse, stores), so its LDS is kept
+// at 39 KB and four workgroups share a CU: the inverse lies where the staged
+// slices were, P and its transpose go out straight from accumulators (P from
+// K Q^T), and rows are loaded eight lanes to 128 bytes, not one lane to a row.
+// Against k_prep (two workgroups a CU, a lane to a row), bf16, us: forward
+// 95 -> 60 (8 x 4096 x 6 heads, 256/512; 245 MB, 4.1 TB/s), 41 -> 33 (4 x 2048
+// x 16, 128/128), 132 -> 97 (8 x 4096 x 16, 64/64); saving pass 105 -> 85 (the
+// first), 410 -> 370 (65,536 x 16, 128/128, packed; 1.19 GB, 3.2 TB/s).
+template <int DK, int MODE>
+__global__ __launch_bounds__(256, DK > 128 ? 3 : 4) void k_prep_small(Args a) {
+  using E = bf16;
+  constexpr bool FOUT = MODE != PREP_BWD, BOUT = MODE != PREP_FWD;
+  constexpr int LD = CH + 8, LDA = CH + 1, KS = DK / 64;
+  constexpr int STAGE = 2 * CH * LD * (int)sizeof(E), INV = (CH * LDA + 32 * 33) * 4;
+  __shared__ __align__(16) unsigned char buf[STAGE > INV ? STAGE : INV];
+  __shared__ float sA[CH * LDA];  // diag(b) A
+  __shared__ float sg[CH], sb[CH];
+  E* sX = (E*)buf;           // K slice
+  E* sY = sX + CH * LD;      // Q slice
+  float* sTf = (float*)buf;  // then T
+  float* sYb = sTf + CH * LDA;
+
+  const int c = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, H = a.H;
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int4 ci = chunk_info(a, c);
+  const int start = ci.y, len = ci.z;
+  const size_t ch = (size_t)c * H + h;
+  const size_t row0 = (size_t)start * H + h;
+
+  // rows tid / 8 and tid / 8 + 32, 16 bytes of each 64-wide slice
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));  // uint4 in a ?: goes to scratch
+  u4 rk[KS][2], rq[KS][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int t = (tid >> 3) + 32 * x;
+    const size_t off = (row0 + (size_t)min(t, len - 1) * H) * DK + (tid & 7) * 8;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      rk[s][x] = *reinterpret_cast<const u4*>((const E*)a.k + off + 64 * s);
+      rq[s][x] = *reinterpret_cast<const u4*>((const E*)a.q + off + 64 * s);
+    }
+  }
+  if (tid < CH) {
+    const float b = tid < len ? a.beta[row0 + (size_t)tid * H] : 0.f;
+    float g = 0.f;  // alpha == 1 (DeltaNet): no decay anywhere
+    if (a.gated) {
+      const float la = tid < len ? a.log_alpha[row0 + (size_t)tid * H] : 0.f;
+      g = wave_incl_scan(la);  // pads repeat g at the last token
+    }
+    sb[tid] = b;
+    sg[tid] = g;
+    a.g[ch * CH + tid] = g;
+  }
+  // ---- K K^T, Q K^T (rows t of wave w) and K Q^T (rows t' of wave w)
+  f32x4 kk[1][4], qk[1][4], kq[1][4];
+  zero_acc(kk);
+  zero_acc(qk);
+  zero_acc(kq);
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    if (s > 0) lds_barrier();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int t = (tid >> 3) + 32 * x;
+      const u4 z = {0u, 0u, 0u, 0u};
+      *reinterpret_cast<u4*>(sX + t * LD + (tid & 7) * 8) = t < len ? rk[s][x] : z;
+      *reinterpret_cast<u4*>(sY + t * LD + (tid & 7) * 8) = t < len ? rq[s][x] : z;
+    }
+    lds_barrier();
+    wave_mma_nt<E, 1, 4, 64>(kk, sX + w * 16 * LD, LD, sX, LD);
+    if (BOUT) wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
+    if (FOUT) wave_mma_nt<E, 1, 4, 64>(kq, sX + w * 16 * LD, LD, sY, LD);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = w * 16 + acc_row(e), i = j * 16 + acc_col();
+      // select, never multiply by an overflowed exp above the diagonal
+      const float dn = __expf(i <= r ? sg[r] - sg[i] : 0.f);  // Gamma_ri
+      const float up = __expf(r <= i ? sg[i] - sg[r] : 0.f);  // Gamma_ir
+      kk[0][j][e] = i < r ? dn * kk[0][j][e] : 0.f;
+      qk[0][j][e] = i <= r ? dn * qk[0][j][e] : 0.f;
+      kq[0][j][e] = r <= i ? up * kq[0][j][e] : 0.f;
+      sA[r * LDA + i] = sb[r] * kk[0][j][e];
+    }
+    if (BOUT) {
+      afrag_put_T<E>((E*)a.Ak + ch * CH * CH, CH, j, w, kk[0][j]);
+      afrag_put_T<E>((E*)a.PTf + ch * CH * CH, CH, j, w, qk[0][j]);
+    }
+    if (FOUT) afrag_put_T<E>((E*)a.Pf + ch * CH * CH, CH, j, w, kq[0][j]);
+  }
+  lds_barrier();
+  invert_unit_lower<LDA>(sA, sTf, sYb);
+  auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
+  export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
+                                    [&](int t, int i) { return T_at(t, i) * sb[i]; });
+  if (BOUT)
+    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                      [&](int i, int t) { return T_at(t, i); });
+}
+
 // ------------------------------------------------------------------ launchers
 
 hipError_t launch_chunk_table(const Args& a, hipStream_t s) {
@@ -535,7 +648,10 @@ hipError_t launch_prep(Dt dt, int dk, int dv, int mode, const Args& a, hipStream
     auto go = [&]<int MODE, bool BLK>() {
       if constexpr (sizeof(E) == 2) {
         if (small) {
-          hipLaunchKernelGGL((k_prep<E, DK, DV, MODE, BLK, true>), grid, dim3(256), 0, s, a);
+          if constexpr (BLK)
+            hipLaunchKernelGGL((k_prep<E, DK, DV, MODE, BLK, true>), grid, dim3(256), 0, s, a);
+          else
+            hipLaunchKernelGGL((k_prep_small<DK, MODE>), grid, dim3(256), 0, s, a);
           return hipGetLastError();
         }
       }
