@@ -100,8 +100,10 @@ __device__ inline void export_afrag_perm_pair(E* dst_raw, E* dst_scaled, const E
 //   T_21 = -T_22 (A_21 T_11)
 // for a block lower-triangular [[T_11, 0], [T_21, T_22]].  sYb: 32 * 33 floats
 // of scratch.  The 16x16 blocks right of the diagonal blocks are not written.
+// Always inlined: as a call its LDS pointers are generic, and the general prep
+// took 37 -> 43 us at 8,000 x 8 heads, 64/64.
 template <int LDA>
-__device__ inline void invert_unit_lower(const float* sA, float* sTf, float* sYb) {
+__device__ __forceinline__ void invert_unit_lower(const float* sA, float* sTf, float* sYb) {
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
   if (tid < CH) {
     const int blk = tid >> 4, j = tid & 15, o = blk * 16;
@@ -531,9 +533,9 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
 // slices were, P and its transpose go out straight from accumulators (P from
 // K Q^T), and rows are loaded eight lanes to 128 bytes, not one lane to a row.
 // Against k_prep (two workgroups a CU, a lane to a row), bf16, us: forward
-// 95 -> 60 (8 x 4096 x 6 heads, 256/512; 245 MB, 4.1 TB/s), 41 -> 33 (4 x 2048
-// x 16, 128/128), 132 -> 97 (8 x 4096 x 16, 64/64); saving pass 105 -> 85 (the
-// first), 410 -> 370 (65,536 x 16, 128/128, packed; 1.19 GB, 3.2 TB/s).
+// 96 -> 55 (8 x 4096 x 6 heads, 256/512; 245 MB, 4.5 TB/s), 41 -> 30 (4 x 2048
+// x 16, 128/128), 132 -> 80 (8 x 4096 x 16, 64/64); saving pass 105 -> 82 (the
+// first), 415 -> 370 (65,536 x 16, 128/128, packed; 1.19 GB, 3.2 TB/s).
 template <int DK, int MODE>
 __global__ __launch_bounds__(256, DK > 128 ? 3 : 4) void k_prep_small(Args a) {
   using E = bf16;
