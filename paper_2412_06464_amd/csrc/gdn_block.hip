@@ -82,12 +82,18 @@ __device__ inline void store_piece(E* p, const float (&v)[N]) {
   }
 }
 
-// Sum over the 64 lanes of a wave (every lane gets it).
+// Sum over the 64 lanes of a wave (every lane gets it; all 64 active), in
+// the order of an xor butterfly: the rows of 16 lanes by DPP, then the rows
+// and the halves by lane swaps (VALU; an LDS permute for each of the two
+// steps waits on the LDS queue instead).
 __device__ inline float wave_sum(float x) {
   x = reduce16(x);
-  x += __shfl_xor(x, 16, 64);
-  x += __shfl_xor(x, 32, 64);
-  return x;
+  auto b = [](float v) { return __builtin_bit_cast(unsigned, v); };
+  auto f = [](unsigned v) { return __builtin_bit_cast(float, v); };
+  const auto r = __builtin_amdgcn_permlane16_swap(b(x), b(x), false, false);
+  x = f(r[0]) + f(r[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap(b(x), b(x), false, false);
+  return f(h[0]) + f(h[1]);
 }
 
 }  // namespace
@@ -103,7 +109,7 @@ template <class E, int D, int DL>
 __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs a) {
   constexpr int CPL = DL / 64, NR = 16 + 3;
   const int c = blockIdx.x, h = blockIdx.y, w = wave_id(), l = lane_id();
-  const int4 ci = a.info[c];
+  const int4 ci = chunk_info(a, c);
   const int n = ci.x, start = ci.y, len = ci.z;
   const int s0 = a.cu ? a.cu[n] : n * a.T;
   const int pos0 = start - s0, r0 = 16 * w, H = a.H;
@@ -155,19 +161,28 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs a) {
   }
 }
 
-// Backward.  Wave w owns rows 16 w .. 16 w + 15, taken in passes of RP rows.
-// A pass walks its rows and the three after them (which may lie in the next
-// chunk of the same sequence), recomputing du_t, so that
-// dx_s = sum_j w_lag(j) du_{s+j} is complete for its own rows; dw is summed
-// over own rows only.  x, du: 4-row sliding windows; raw rows prefetched.
+// Backward.  Wave w walks its rows 16 w .. 16 w + 15 in passes of RP rows,
+// loaded together; du_t of a row, and with it dx of the row three before:
+//   dx_s = sum_j w_lag(j) du_{s+j}
+// so the last three rows' dx wait for the next three du.  Those are the next
+// wave's first three, passed through LDS; only the last wave of a chunk that
+// the sequence continues past recomputes them from the next chunk's rows.
+// Bound by memory and VALU work alike (64 lanes x D/64 channels, ~40
+// instructions a channel and row, against 6 bytes).
+// Against passes of 8 rows that each recomputed the three du after them (1.4
+// rows' work and 1.6 rows' loads a row), bf16, with the sums of dw, us: q and k
+// 209 -> 193, v 169 -> 164 (8 x 4096 x 6, 256/512; v: 604 MB, 3.9 TB/s), q and
+// k 113 -> 94 (20,000 x 8, 128/128, packed).  Passes of 4 rows, or four waves
+// a SIMD by a register limit, are within 3% either way.
 template <class E, int D, int DL>
 __global__ __launch_bounds__(256) void k_conv_bwd(ConvArgs a) {
   constexpr int CPL = DL / 64;
   constexpr int RP = 8;  // rows per pass
-  constexpr int NX = RP + 6, NG = RP + 3;
-  __shared__ float sdw[4][DL][4];
-  const int c = blockIdx.x, h = blockIdx.y, w = wave_id(), l = lane_id();
-  const int4 ci = a.info[c];
+  // du of the first three rows of waves 1 .. 3, then the waves' sums of dw
+  __shared__ __align__(16) float lds[4 * DL * 4];
+  const int c = blockIdx.x, h = blockIdx.y, l = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int4 ci = chunk_info(a, c);
   const int n = ci.x, start = ci.y, len = ci.z;
   const int s0 = a.cu ? a.cu[n] : n * a.T;
   const int L = a.cu ? a.cu[n + 1] - s0 : a.T;
@@ -187,90 +202,136 @@ __global__ __launch_bounds__(256) void k_conv_bwd(ConvArgs a) {
   const E* X = (const E*)a.x;
   const E* DY = (const E*)a.dy;
   E* DX = (E*)a.dx;
+  auto load_x = [&](RowRaw<E, CPL>& x, int r) {
+    if (pos0 + r >= 0 && pos0 + r < L)
+      x.load(X + ((size_t)(start + r) * H + h) * D + ch);
+    else
+      x.zero();
+  };
+  auto load_dy = [&](RowRaw<E, CPL>& x, int r) {
+    if (pos0 + r < L)
+      x.load(DY + ((size_t)(start + r) * H + h) * D + ch);
+    else
+      x.zero();
+  };
 
-  for (int r0 = 16 * w; r0 < 16 * w + 16 && r0 < len; r0 += RP) {
-    RowRaw<E, CPL> xr[NX], gr[NG];  // x rows r0-3 .. r0+RP+2, dy rows r0 .. r0+RP+2
+  float xw[4][CPL], dw4[4][CPL];  // x_{t-3} .. x_t;  du_{t-3} .. du_t
 #pragma unroll
-    for (int i = 0; i < NX; ++i) {
-      const int r = r0 - 3 + i, p = pos0 + r;
-      if (p >= 0 && p < L)
-        xr[i].load(X + ((size_t)(start + r) * H + h) * D + ch);
-      else
-        xr[i].zero();
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) xw[q][k] = dw4[q][k] = 0.f;
+  auto shift = [](float (&v)[4][CPL]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) v[q][k] = v[q + 1][k];
+  };
+  // x and du of the next row r into the windows
+  auto step = [&](const RowRaw<E, CPL>& x, const RowRaw<E, CPL>& dy, int r) {
+    const bool valid = pos0 + r < L;  // uniform over the wave
+    shift(xw);
+    shift(dw4);
+    x.to_float(xw[3]);
+    float gy[CPL], u[CPL], z[CPL], sg[CPL], ss = 0.f, zg = 0.f;
+    dy.to_float(gy);
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+      u[k] = wl[k][0] * xw[3][k] + wl[k][1] * xw[2][k] + wl[k][2] * xw[1][k] + wl[k][3] * xw[0][k];
+      sg[k] = sigmoidf(u[k]);
+      z[k] = u[k] * sg[k];
+      ss += z[k] * z[k];
+      zg += z[k] * gy[k];
+    }
+    float sc = 1.f, yg = 0.f;
+    if (a.l2) {
+      sc = rsqrtf(wave_sum(ss) + a.eps);  // 1 / |z|
+      yg = wave_sum(zg) * sc;             // y . dy
     }
 #pragma unroll
-    for (int i = 0; i < NG; ++i) {
-      const int r = r0 + i;
-      if (pos0 + r < L)
-        gr[i].load(DY + ((size_t)(start + r) * H + h) * D + ch);
-      else
-        gr[i].zero();
+    for (int k = 0; k < CPL; ++k) {
+      const float dz = a.l2 ? (gy[k] - z[k] * sc * yg) * sc : gy[k];
+      dw4[3][k] = valid ? dz * sg[k] * (1.f + u[k] * (1.f - sg[k])) : 0.f;
     }
-    float xw[4][CPL], dw4[4][CPL];  // x_{t-3} .. x_t;  du_{t-3} .. du_t
+  };
+  auto put_dx = [&](int r) {  // of row r, the windows' oldest
+    float dx[CPL];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int k = 0; k < CPL; ++k)
+      dx[k] = wl[k][0] * dw4[0][k] + wl[k][1] * dw4[1][k] + wl[k][2] * dw4[2][k] +
+              wl[k][3] * dw4[3][k];
+    store_piece<E, CPL>(DX + ((size_t)(start + r) * H + h) * D + ch, dx);
+  };
+
+  const int r0 = 16 * w;
+  int re = r0;                   // one past the rows walked
+  RowRaw<E, CPL> xn[3], gn[3];   // the three rows after the chunk
+  if (r0 < len) {
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) xw[q][k] = dw4[q][k] = 0.f;
+    for (int q = 0; q < 3; ++q) {
+      RowRaw<E, CPL> x;
+      load_x(x, r0 - 3 + q);
+      x.to_float(xw[q + 1]);
+    }
+#pragma unroll 1
+    for (; re < r0 + 16 && re < len; re += RP) {
+      RowRaw<E, CPL> xr[RP], gr[RP];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) xr[i].to_float(xw[i + 1]);
+      for (int i = 0; i < RP; ++i) {
+        load_x(xr[i], re + i);
+        load_dy(gr[i], re + i);
+      }
+      if (re == CH - RP) {
 #pragma unroll
-    for (int i = 0; i < NG; ++i) {
-      const int r = r0 + i;
-      const bool valid = pos0 + r < L;  // uniform over the wave
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-          xw[q][k] = xw[q + 1][k];
-          dw4[q][k] = dw4[q + 1][k];
+        for (int q = 0; q < 3; ++q) {
+          load_x(xn[q], CH + q);
+          load_dy(gn[q], CH + q);
         }
-      xr[i + 3].to_float(xw[3]);
-      float gy[CPL], u[CPL], z[CPL], sg[CPL], ss = 0.f, zg = 0.f;
-      gr[i].to_float(gy);
-#pragma unroll
-      for (int k = 0; k < CPL; ++k) {
-        u[k] = wl[k][0] * xw[3][k] + wl[k][1] * xw[2][k] + wl[k][2] * xw[1][k] + wl[k][3] * xw[0][k];
-        sg[k] = sigmoidf(u[k]);
-        z[k] = u[k] * sg[k];
-        ss += z[k] * z[k];
-        zg += z[k] * gy[k];
-      }
-      float sc = 1.f, yg = 0.f;
-      if (a.l2) {
-        sc = rsqrtf(wave_sum(ss) + a.eps);  // 1 / |z|
-        yg = wave_sum(zg) * sc;             // y . dy
       }
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) {
-        const float dz = a.l2 ? (gy[k] - z[k] * sc * yg) * sc : gy[k];
-        dw4[3][k] = valid ? dz * sg[k] * (1.f + u[k] * (1.f - sg[k])) : 0.f;
-      }
-      if (i < RP && r < len) {  // own row: dw over x_{t-j}
+      for (int i = 0; i < RP; ++i) {
+        const int r = re + i;
+        step(xr[i], gr[i], r);
+        if (r < len) {  // dw over x_{t-j}
 #pragma unroll
-        for (int k = 0; k < CPL; ++k)
+          for (int k = 0; k < CPL; ++k)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) dwp[k][j] += dw4[3][k] * xw[3 - j][k];
-      }
-      if (i >= 3 && r - 3 < len) {  // dx of row r - 3 is complete
-        float dx[CPL];
+            for (int j = 0; j < 4; ++j) dwp[k][j] += dw4[3][k] * xw[3 - j][k];
+        }
+        if (i < 3 && w > 0 && re == r0) {
 #pragma unroll
-        for (int k = 0; k < CPL; ++k)
-          dx[k] = wl[k][0] * dw4[0][k] + wl[k][1] * dw4[1][k] + wl[k][2] * dw4[2][k] +
-                  wl[k][3] * dw4[3][k];
-        store_piece<E, CPL>(DX + ((size_t)(start + r - 3) * H + h) * D + ch, dx);
+          for (int k = 0; k < CPL; ++k) lds[((w - 1) * 3 + i) * DL + cl + k] = dw4[3][k];
+        }
+        if (r >= r0 + 3 && r - 3 < len) put_dx(r - 3);
       }
     }
   }
+  __syncthreads();
+  if (r0 < len) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int r = re + q;
+      if (r >= CH) {
+        step(xn[q], gn[q], r);
+      } else {
+        shift(dw4);
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) dw4[3][k] = r < len ? lds[(w * 3 + q) * DL + cl + k] : 0.f;
+      }
+      if (r - 3 < len) put_dx(r - 3);
+    }
+  }
+  __syncthreads();  // du is read
 #pragma unroll
   for (int k = 0; k < CPL; ++k)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) sdw[w][cl + k][j] = dwp[k][j];
+    for (int j = 0; j < 4; ++j) lds[(w * DL + cl + k) * 4 + j] = dwp[k][j];
   __syncthreads();
   // this workgroup's partial dw[h][ch][tap], in the order of the weights
   float* part = a.part + (((size_t)c * H + h) * D + blockIdx.z * DL) * a.W;
   for (int idx = threadIdx.x; idx < DL * a.W; idx += 256) {
     const int cc = idx / a.W, tap = idx - cc * a.W, j = a.W - 1 - tap;
-    part[idx] = sdw[0][cc][j] + sdw[1][cc][j] + sdw[2][cc][j] + sdw[3][cc][j];
+    const float* s = lds + cc * 4 + j;
+    part[idx] = s[0] + s[DL * 4] + s[2 * DL * 4] + s[3 * DL * 4];
   }
 }
 
@@ -284,6 +345,7 @@ __global__ __launch_bounds__(256) void k_sum_rows(const float* in, int N, int M,
   const int i0 = blockIdx.y * SUM_RS, i1 = min(N, i0 + SUM_RS);
   float acc = 0.f;
   if (m < M)
+#pragma unroll 8
     for (int i = i0 + seg; i < i1; i += 16) acc += in[(size_t)i * M + m];
   s[seg][ml] = acc;
   __syncthreads();
