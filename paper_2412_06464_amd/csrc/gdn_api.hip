@@ -851,7 +851,8 @@ static gdn_status conv_call(const gdn_problem* p, int dim, int width, int l2norm
   a.dx = dx;
   a.dw = dw;
   const Dt dt = p->dtype == GDN_F32 ? Dt::F32 : Dt::BF16;
-  hipError_t e = gdn::launch_chunk_table(t, (hipStream_t)stream);
+  // the chunk table serves packed input only; dense chunks are arithmetic
+  hipError_t e = t.cu ? gdn::launch_chunk_table(t, (hipStream_t)stream) : hipSuccess;
   if (e == hipSuccess)
     e = bwd ? gdn::launch_conv_bwd(dt, dim, a, (hipStream_t)stream)
             : gdn::launch_conv_fwd(dt, dim, a, (hipStream_t)stream);

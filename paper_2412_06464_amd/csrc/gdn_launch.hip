@@ -192,8 +192,7 @@ hipError_t launch_bwd_saved(Dt dt, int dk, int dv, const Args& a, hipStream_t s,
 }
 
 // Backward of the fused block from a saving fused forward's buffer.  The
-// chunk table is built for dense input too: the v prologue's backward reads
-// it.  The reverse pass writes the rule's dv (a.dv, a temporary here), the
+// reverse pass writes the rule's dv (a.dv, a temporary here), the
 // gradient kernel folds in the q and k prologue, the fix-up finishes dx
 // across chunk boundaries and sums dw, and the v prologue's backward runs
 // on the rule's dv.
@@ -202,7 +201,9 @@ hipError_t launch_block_bwd_saved(int dk, int dv, const Args& a, const ConvArgs&
                                   Timing* t) {
   if (audit(Seq::BlockBwdSaved, a) >= 0) return hipErrorInvalidValue;
   hipError_t e;
-  if ((e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) != hipSuccess)
+  // the chunk table serves packed input only; dense chunks are arithmetic
+  if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
+                  hipSuccess)
     return e;
   if ((e = timed(t, "k_bwd_seq", s, [&] { return launch_bwd_seq(Dt::BF16, dk, dv, a, s); })) !=
       hipSuccess)

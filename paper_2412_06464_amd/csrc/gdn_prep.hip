@@ -30,37 +30,53 @@
 
 namespace gdn {
 
-// One workgroup of 256 threads.  Sequences are taken 256 at a time: thread
-// i reads the bounds of sequence base + i, an exclusive scan of the chunk
-// counts in LDS (plus the running total of the earlier groups) gives its
-// first chunk, and the thread writes that sequence's chunk entries.
-__global__ void k_chunk_table(const int32_t* cu, int N, int T, int4* info, int* seq_chunk0) {
-  __shared__ int scan[2][256];
-  const int tid = threadIdx.x;
+// Workgroup b of 256 threads writes chunks 256 b .. 256 b + 255.  Every
+// workgroup scans the sequences' chunk counts, 256 at a time (thread i has
+// sequence base + i), and a thread finds its chunk's sequence by bisection.
+// Bound by latency: one workgroup whose threads wrote a whole sequence's
+// chunks each took 12 us where this takes 6 (65,536 tokens, 21 sequences), and
+// the kernels that read the table were slower behind it (saving prep 370 -> 334,
+// gradient 991 -> 956 us at x 16 heads, 128/128).
+__global__ __launch_bounds__(256) void k_chunk_table(const int32_t* cu, int N, int4* info,
+                                                     int* seq_chunk0) {
+  __shared__ int first[256], start[256], length[256], wsum[4];
+  const int tid = threadIdx.x, w = tid >> 6, c = blockIdx.x * 256 + tid;
   int carry = 0;  // chunks of the sequences before this group
   for (int base = 0; base < N; base += 256) {
     const int n = base + tid;
-    const int s = n < N ? (cu ? cu[n] : n * T) : 0;
-    const int L = n < N ? (cu ? cu[n + 1] - s : T) : 0;
-    const int c = (L + CH - 1) / CH;
-    // inclusive Hillis-Steele scan of c over the 256 threads
-    int p = 0;
-    scan[p][tid] = c;
+    const int s = n < N ? cu[n] : 0, L = n < N ? cu[n + 1] - s : 0;
+    const int cnt = (L + CH - 1) / CH;
+    int x = cnt;  // inclusive scan
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(x, d, 64);
+      if (lane_id() >= d) x += y;
+    }
+    if (lane_id() == 63) wsum[w] = x;
     __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-      scan[p ^ 1][tid] = scan[p][tid] + (tid >= d ? scan[p][tid - d] : 0);
-      p ^= 1;
-      __syncthreads();
+    int before = carry, end = carry;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i < w) before += wsum[i];
+      end += wsum[i];
     }
-    const int c0 = carry + scan[p][tid] - c;
-    if (n < N) {
-      seq_chunk0[n] = c0;
-      for (int j = 0; j < c; ++j) info[c0 + j] = make_int4(n, s + j * CH, min(CH, L - j * CH), 0);
+    first[tid] = before + x - cnt;
+    start[tid] = s;
+    length[tid] = L;
+    if (blockIdx.x == 0 && n < N) seq_chunk0[n] = before + x - cnt;
+    __syncthreads();
+    if (c >= carry && c < end) {
+      int i = 0;  // the last sequence that starts at or before chunk c: it is not empty
+#pragma unroll
+      for (int d = 128; d > 0; d >>= 1)
+        if (first[i + d] <= c) i += d;
+      const int j = (c - first[i]) * CH;
+      info[c] = make_int4(base + i, start[i] + j, min(CH, length[i] - j), 0);
     }
-    carry += scan[p][255];
-    __syncthreads();  // the scan buffers are reused by the next group
+    carry = end;
+    __syncthreads();  // the buffers are reused by the next group
   }
-  if (tid == 0) seq_chunk0[N] = carry;
+  if (blockIdx.x == 0 && tid == 0) seq_chunk0[N] = carry;
 }
 
 // ------------------------------------------------------------------ prep
@@ -633,7 +649,7 @@ __global__ __launch_bounds__(256, DK > 128 ? 3 : 4) void k_prep_small(Args a) {
 // ------------------------------------------------------------------ launchers
 
 hipError_t launch_chunk_table(const Args& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_chunk_table, dim3(1), dim3(256), 0, s, a.cu, a.N, a.T, a.info,
+  hipLaunchKernelGGL(k_chunk_table, dim3((a.NC + 255) / 256), dim3(256), 0, s, a.cu, a.N, a.info,
                      a.seq_chunk0);
   return hipGetLastError();
 }
