@@ -34,9 +34,7 @@ namespace gdn {
 // workgroup scans the sequences' chunk counts, 256 at a time (thread i has
 // sequence base + i), and a thread finds its chunk's sequence by bisection.
 // Bound by latency: one workgroup whose threads wrote a whole sequence's
-// chunks each took 12 us where this takes 6 (65,536 tokens, 21 sequences), and
-// the kernels that read the table were slower behind it (saving prep 370 -> 334,
-// gradient 991 -> 956 us at x 16 heads, 128/128).
+// chunks each took 12 us where this takes 6 (65,536 tokens, 21 sequences).
 __global__ __launch_bounds__(256) void k_chunk_table(const int32_t* cu, int N, int4* info,
                                                      int* seq_chunk0) {
   __shared__ int first[256], start[256], length[256], wsum[4];
