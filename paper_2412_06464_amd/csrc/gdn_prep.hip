@@ -220,6 +220,27 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   constexpr int EPV = 16 / sizeof(E), NI = 64 / EPV / 4;
   constexpr int KS = DK / 64, VS = DV / 64;
   uint4 rk[KS][NI], rq[KS][NI], rv[VS][NI];
+  // a slice of raw rows into LDS, row-major (dst[t][c]) or transposed
+  // (dst[c][t], element scaled by scale)
+  auto put_rows = [&](E* dst, const uint4 (&r)[NI]) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      *reinterpret_cast<uint4*>(dst + lane_id() * LD + (w + 4 * i) * EPV) = r[i];
+  };
+  // a row-major slice from LDS to columns c0 .. c0 + 63 of y [token][H][D],
+  // eight lanes to a row's 128 bytes: a lane to a row, as the prologue holds
+  // its results, takes the memory path four times as long (prep of
+  // the fused block with q, k and v written, us: 360 -> 303 at 8 x 4096 x 6,
+  // 256/512; 141 -> 134 at 20,000 x 8, 128/128)
+  auto rows_out = [&](const E* src, void* y, int D, int c0) {
+#pragma unroll
+    for (int x = 0; x < 64 * CH / EPV / 256; ++x) {
+      const int u = tid + 256 * x, t = u / (64 / EPV), cv = u % (64 / EPV);
+      if (t < len)
+        *reinterpret_cast<uint4*>((E*)y + (row0 + (size_t)t * H) * D + c0 + cv * EPV) =
+            *reinterpret_cast<const uint4*>(src + t * LD + cv * EPV);
+    }
+  };
   if constexpr (!BLK) {
     const int t = lane_id();
     const bool tv = t < len;
@@ -301,7 +322,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
       }
     };
     // one tensor with a row norm (q or k): out[sl][i] = y
-    auto prologue_l2 = [&](const E* X, const float4* wt, uint4 (&out)[KS][NI], void* yout) {
+    auto prologue_l2 = [&](const E* X, const float4* wt, uint4 (&out)[KS][NI]) {
       float z[KS][NI][EPV], ss = 0.f;
       st.fetch(X, DK, H, h, start, len, nprev, 0, tid);
 #pragma unroll
@@ -322,13 +343,10 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
 #pragma unroll
           for (int q = 0; q < EPV; ++q) z[sl][i][q] *= sc;
           out[sl][i] = pack(z[sl][i]);
-          if (yout && t < len)
-            *reinterpret_cast<uint4*>((E*)yout + (row0 + (size_t)t * H) * DK + 64 * sl +
-                                      (w + 4 * i) * EPV) = out[sl][i];
         }
     };
-    prologue_l2((const E*)a.xq, sWl, rq, a.yq);
-    prologue_l2((const E*)a.xk, sWl + DK, rk, a.yk);
+    prologue_l2((const E*)a.xq, sWl, rq);
+    prologue_l2((const E*)a.xk, sWl + DK, rk);
     {  // v: no norm
       const E* X = (const E*)a.xv;
       const float4* wt = sWl + 2 * DK;
@@ -338,25 +356,22 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
         float z[NI][EPV];
         slice_z(X, DV, wt, sl, VS, z);
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          rv[sl][i] = pack(z[i]);
-          if (a.yv && t < len)
-            *reinterpret_cast<uint4*>((E*)a.yv + (row0 + (size_t)t * H) * DV + 64 * sl +
-                                      (w + 4 * i) * EPV) = rv[sl][i];
+        for (int i = 0; i < NI; ++i) rv[sl][i] = pack(z[i]);
+        // the slice before went to LDS ahead of this one's barriers
+        if (a.yv) {
+          if (sl > 0) rows_out((sl & 1) ? sX : sY, a.yv, DV, 64 * (sl - 1));
+          put_rows((sl & 1) ? sY : sX, rv[sl]);
         }
       }
     }
     if constexpr (WARM) wait_vmcnt<0>();  // the warm-up's loads into sWarm have landed
     lds_barrier();    // A and T are formed below
+    if (a.yv) {
+      rows_out((VS & 1) ? sX : sY, a.yv, DV, DV - 64);
+      lds_barrier();
+    }
   }
 
-  // a slice of raw rows into LDS, row-major (dst[t][c]) or transposed
-  // (dst[c][t], element scaled by scale)
-  auto put_rows = [&](E* dst, const uint4 (&r)[NI]) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      *reinterpret_cast<uint4*>(dst + lane_id() * LD + (w + 4 * i) * EPV) = r[i];
-  };
   auto put_T = [&](E* dstT, const uint4 (&r)[NI], float scale) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -403,6 +418,10 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     put_rows(sX, rk[s]);
     put_rows(sY, rq[s]);
     lds_barrier();
+    if constexpr (BLK) {
+      if (a.yk) rows_out(sX, a.yk, DK, 64 * s);
+      if (a.yq) rows_out(sY, a.yq, DK, 64 * s);
+    }
     wave_mma_nt<E, 1, 4, 64>(kk, sX + w * 16 * LD, LD, sX, LD);
     wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
     if (FOUT && !SMALL) {
