@@ -215,17 +215,25 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   const E* V = (const E*)a.v + row0 * DV;
 
   // The chunk's raw k, q and v rows, loaded once at the start and kept in
-  // registers for both the row-major and the transposed staging: lane = row
-  // t, 16-byte vectors cv = w + 4 i of each 64-wide column slice.
+  // registers for both the row-major and the transposed staging: row rt and
+  // 16-byte vectors rc + 4 i of each 64-wide column slice.  As loaded, a
+  // quad of lanes holds 64 bytes of one row (a lane to a row, as the block
+  // prologue forms them, takes the memory path four times as long; whole
+  // 128-byte lines would meet the same banks four times in the transposed
+  // staging, where this does twice).
+  // Prep, us, against a lane to a row: fp32 saving 155 -> 147 (2 x 2048 x 6,
+  // 256/512), fp32 222 -> 212 (4 x 2048 x 16, 128/128), bf16 saving 37.5 -> 36
+  // (8,000 x 8, 64/64).
   constexpr int EPV = 16 / sizeof(E), NI = 64 / EPV / 4;
   constexpr int KS = DK / 64, VS = DV / 64;
+  const int rt = BLK ? lane_id() : 16 * w + (lane_id() >> 2), rc = BLK ? w : lane_id() & 3;
   uint4 rk[KS][NI], rq[KS][NI], rv[VS][NI];
   // a slice of raw rows into LDS, row-major (dst[t][c]) or transposed
   // (dst[c][t], element scaled by scale)
   auto put_rows = [&](E* dst, const uint4 (&r)[NI]) {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      *reinterpret_cast<uint4*>(dst + lane_id() * LD + (w + 4 * i) * EPV) = r[i];
+      *reinterpret_cast<uint4*>(dst + rt * LD + (rc + 4 * i) * EPV) = r[i];
   };
   // a row-major slice from LDS to columns c0 .. c0 + 63 of y [token][H][D],
   // eight lanes to a row's 128 bytes: a lane to a row, as the prologue holds
@@ -242,14 +250,14 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     }
   };
   if constexpr (!BLK) {
-    const int t = lane_id();
+    const int t = rt;
     const bool tv = t < len;
     const size_t ko = (size_t)(tv ? t : 0) * H * DK, vo = (size_t)(tv ? t : 0) * H * DV;
 #pragma unroll
     for (int sl = 0; sl < KS; ++sl)
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        const int c = 64 * sl + (w + 4 * i) * EPV;
+        const int c = 64 * sl + (rc + 4 * i) * EPV;
         rk[sl][i] = tv ? *reinterpret_cast<const uint4*>(K + ko + c) : uint4{0u, 0u, 0u, 0u};
         rq[sl][i] = tv ? *reinterpret_cast<const uint4*>(Q + ko + c) : uint4{0u, 0u, 0u, 0u};
       }
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     for (int sl = 0; sl < VS; ++sl)
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        const int c = 64 * sl + (w + 4 * i) * EPV;
+        const int c = 64 * sl + (rc + 4 * i) * EPV;
         rv[sl][i] = tv ? *reinterpret_cast<const uint4*>(V + vo + c) : uint4{0u, 0u, 0u, 0u};
       }
   }
@@ -382,7 +390,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
       x.u = r[i];
 #pragma unroll
       for (int j = 0; j < EPV; ++j)
-        dstT[((w + 4 * i) * EPV + j) * LD + lane_id()] = to_e<E>(to_f(x.e[j]) * scale);
+        dstT[((rc + 4 * i) * EPV + j) * LD + rt] = to_e<E>(to_f(x.e[j]) * scale);
     }
   };
 
@@ -544,7 +552,7 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   });
 
   // ---- dv slices: U~ = T (b V), accumulator layout
-  const float bt = sb[lane_id()];
+  const float bt = sb[rt];
   static_for<0, SMALL ? 0 : VS>([&](auto sc) {
     constexpr int s = decltype(sc)::value;
     put_T(sX, rv[s], bt);  // sX[v][t] = b_t V
