@@ -24,6 +24,9 @@
 //                  for the reverse pass K, P^T, T^T, -W~^T, (e^g Q)^T, plus
 //                  strictLower(Gamma K K^T)^T for the gradient kernel.
 //                  Forward with save: both sets.
+//   k_prep_small   the same ahead of the bf16 passes of gdn_chain.h, which read
+//                  q, k and v themselves: g, T diag(b) and P; for the backward
+//                  P^T, T^T and strictLower(Gamma K K^T)^T.
 #include "gdn_device.h"
 #include "gdn_kernels.h"
 #include "gdn_prologue.h"
