@@ -31,8 +31,15 @@
 // operands; with NC = 2, column c of tile j is 8 (c >> 2) + 4 j + (c & 3) of
 // the wave's 32, so that a transposed product leaves eight consecutive columns
 // in a lane, one 16-byte store.  Contractions over t use the order of
-// kperm<bf16>, as the prep kernel stores T and P.  A transpose is a product
-// with a 0/1 matrix: exact, and it needs no LDS.
+// kperm<bf16>, as the prep kernel stores T and P.  The state, V' and dS go out
+// transposed by a product with a 0/1 matrix, which needs no LDS and is exact
+// where they are finite.  Where one is not, 0 Inf = NaN reaches the other 31
+// rows of its own column in the stored copy, which only the gradient kernel
+// reads; that column's V' (or dX) is then not finite in any row of the chunk
+// either, since K S contracts over the state's rows, and with it none of the
+// gradients that the copy enters.  v and dO, whose columns stay apart through
+// the whole recurrence, are turned by transposed LDS reads instead, which
+// move values and keep a non-finite one in its column.
 #pragma once
 #include "gdn_device.h"
 #include "gdn_kernels.h"
@@ -249,13 +256,8 @@ struct Tri {
 template <int NC, bool STREAM = true>
 struct Cols {
   static constexpr int W = 16 * NC;
-  int v0;      // first column
-  frag sel[NC];  // B operand that picks tile j's columns out of the wave's (VRows)
-  __device__ inline Cols(int first) : v0(first) {
-    const int g = lane_id() >> 4;
-#pragma unroll
-    for (int j = 0; j < NC; ++j) sel[j] = select8(4 * NC * g, at(j));
-  }
+  int v0;  // first column
+  __device__ inline Cols(int first) : v0(first) {}
   __device__ static inline int at(int j) {  // column of this lane in tile j, from v0
     const int c = lane_id() & 15;
     return NC == 2 ? 8 * (c >> 2) + 4 * j + (c & 3) : c;
@@ -295,13 +297,14 @@ struct Cols {
 };
 
 // One 16-row tile of a wave's columns, 64 lanes of 8 NC bytes, passed through
-// LDS between the two lane orders: memory order (lane 4 r + p holds piece p of
-// row r: four lanes cover a row's 32 NC bytes, which the memory path takes as
-// one access) and operand order (lane 16 p + r).  In operand order straight
-// from or to memory every lane of a quad is another row, four times the
-// accesses: with v and O so, a chunk at dk = 128 took 9.2k cycles and 6.6k /
-// 6.9k without the loads of v / the stores of O.  The unit of (r, p) is
-// permuted so that both sides are free of bank conflicts.
+// LDS between memory order (lane 4 r + p holds piece p of row r: four lanes
+// cover a row's 32 NC bytes, which the memory path takes as one access) and
+// the lane orders of the products: operand order (lane 16 p + r) for the rows
+// that go out, and accumulator tiles (transposed reads) for those that come
+// in.  In operand order straight from or to memory every lane of a quad is
+// another row, four times the accesses: with v and O so, a chunk at dk = 128
+// took 9.2k cycles and 6.6k / 6.9k without the loads of v / the stores of O.
+// The unit of (r, p) is permuted so that all sides are free of bank conflicts.
 template <int NC>
 struct Bounce {
   typedef unsigned vec __attribute__((ext_vector_type(2 * NC)));
@@ -318,18 +321,20 @@ struct Bounce {
   }
   __device__ static inline void put(unsigned at, vec v) { *(lds_vec*)(uintptr_t)at = v; }
   __device__ static inline vec get(unsigned at) { return *(const lds_vec*)(uintptr_t)at; }
+  // rows 4 (l >> 4) .. + 3 of this lane's column in tile c: a lane points at
+  // its piece of the 16 lanes' 4 rows, which in memory order is its own unit
+  __device__ inline s16x4 column(int c) const {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(mem + 8 * c));
+  }
 };
 
-// Rows of v or dO as A operands (lane = row of tile i), zero past the
-// chunk's end, and their product with the wave's selection matrix:
-// accumulator tiles of the rows (tile i, rows t; tile c, the wave's columns).
-// The 32 columns of a wave are one k-step of 32; 16 columns take the half-wide
-// product.
+// Rows of v or dO as accumulator tiles (tile i, rows t; tile c, the wave's
+// columns), zero past the chunk's end.
 template <int NC>
 struct VRows {
   using B = Bounce<NC>;
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typename B::vec r[4];
+  typename B::vec r[4];  // as loaded
+  s16x4 t[4][NC];        // turned
   // x: the chunk's first row and head at the wave's first column
   __device__ inline void load(const bf16* x, unsigned rs, int len) {
     const unsigned l = lane_id(), u = (l & 3) * (8 * NC), lim = (len - 1) * rs + u;
@@ -337,7 +342,6 @@ struct VRows {
     for (int i = 0; i < 4; ++i)
       r[i] = ld<typename B::vec>(x, min((l >> 2) * rs + u + 16 * i * rs, lim));
   }
-  // from memory to operand order
   __device__ inline void turn(const B& b, int len) {
     if (len < CH) {
 #pragma unroll
@@ -347,16 +351,20 @@ struct VRows {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       B::put(b.mem, r[i]);
-      r[i] = B::get(b.op);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) t[i][c] = b.column(c);
     }
   }
-  __device__ inline f32x4 add(int i, frag sel, f32x4 c) const {
-    if constexpr (NC == 2) {
-      return M::mma(__builtin_bit_cast(frag, r[i]), sel, c);
-    } else {
-      const s16x4 s = __builtin_bit_cast(s16x4, __builtin_shufflevector(sel, sel, 0, 1, 2, 3));
-      return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, r[i]), s, c, 0, 0, 0);
-    }
+  __device__ inline f32x4 tile(int i, int c) const {
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = (float)__builtin_bit_cast(bf16, (short)t[i][c][e]);
+    return x;
+  }
+  // row tiles 2 kt, 2 kt + 1 as an operand over t
+  __device__ inline frag over_t(int kt, int c) const {
+    return __builtin_bit_cast(
+        frag, __builtin_shufflevector(t[2 * kt][c], t[2 * kt + 1][c], 0, 1, 2, 3, 4, 5, 6, 7));
   }
 };
 
@@ -650,11 +658,7 @@ void k_fwd_chain(Args a) {
     for (int i = 0; i < 4; ++i) egr[i] = *reinterpret_cast<const f32x4*>(&gate[0][16 * i + 4 * g]);
     auto residual = [&](int i) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) X[i][c][e] *= -egr[i][e];
-        X[i][c] = vr.add(i, cols.sel[c], X[i][c]);
-      }
+      for (int c = 0; c < NC; ++c) X[i][c] = vr.tile(i, c) - egr[i] * X[i][c];
     };
     if constexpr (OUT) {
       static_for<0, LAG>([&](auto qc) {
@@ -950,18 +954,12 @@ void k_bwd_chain(Args a) {
     frag dOb[2][NC], dOg[2][NC];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
-      f32x4 d[2][NC];
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          d[p][c] = dor.add(2 * kt + p, cols.sel[c], f32x4{0.f, 0.f, 0.f, 0.f});
       const f32x4 e0 = *reinterpret_cast<const f32x4*>(&gate[0][32 * kt + 4 * g]);
       const f32x4 e1 = *reinterpret_cast<const f32x4*>(&gate[0][32 * kt + 16 + 4 * g]);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        dOb[kt][c] = pack8(d[0][c], d[1][c]);
-        dOg[kt][c] = pack8(d[0][c] * e0, d[1][c] * e1);
+        dOb[kt][c] = dor.over_t(kt, c);
+        dOg[kt][c] = pack8(dor.tile(2 * kt, c) * e0, dor.tile(2 * kt + 1, c) * e1);
       }
     }
     phase();

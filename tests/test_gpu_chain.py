@@ -9,7 +9,7 @@ import torch
 
 from paper_2412_06464_amd.inputs import make_inputs
 from tests.test_gpu_parity import (G, TOL, check_bwd, check_fwd, check_saved, run_bwd, run_fwd,
-                                   run_saved, to_dev)  # noqa: F401
+                                   run_saved, say, to_dev)  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,52 @@ def test_chain_passes_gates(G, oracle_mod, dk, dv, B, H, T, kw):
     assert torch.equal(o, o2) and torch.equal(ht, ht2)
     for name in r:
         assert torch.equal(r[name], r2[name]), name
+
+
+def training_step(G, d):
+    o, ht, r = run_saved(G, d)
+    return dict(r, o=o, ht=ht)
+
+
+PLANTS = [("v", float("nan")), ("v", float("inf")), ("dO", float("nan")), ("dO", float("-inf")),
+          ("h0", float("inf")), ("dht", float("nan")), ("dht", float("inf")), ("q", float("nan")),
+          ("k", float("inf")), ("beta", float("nan")), ("log_alpha", float("nan"))]
+
+
+@pytest.mark.parametrize("dk,dv,B,H,T", [(256, 512, 2, 6, 150), (256, 512, 3, 14, 150),
+                                         (128, 128, 10, 6, 150), (128, 128, 11, 16, 150),
+                                         (64, 64, 8, 13, 150)])
+def test_nonfinite_values_reach_no_further(G, dk, dv, B, H, T):
+    """A NaN or infinity in one input of one unit changes, of that unit's
+    outputs, nothing that it leaves unchanged where the unit is computed alone
+    (by the passes that run few sequence-heads), and nothing of any other
+    unit: a value of v or dO, above all, stays in its own column of o, ht, dv
+    and dh0.  It lies in the middle one of three chunks."""
+    inp = problem(dk, dv, B, H, T, seed=33, h0_std=0.05, backward=True)
+    b, h = B - 1, H - 2
+    cut = lambda x, n: x[b:b + 1, h:h + 1] if n in ("h0", "dht", "dh0", "ht") else x[b:b + 1, :, h:h + 1]
+    alone = {n: cut(x, n).contiguous() if isinstance(x, torch.Tensor) else x
+             for n, x in inp.items()}
+    clean, clean1 = training_step(G, to_dev(inp)), training_step(G, to_dev(alone))
+    for name, value in PLANTS:
+        say("plant", dk, dv, B * H, name, value)
+        planted = {}
+        for key, src in (("all", inp), ("one", alone)):
+            bb, hh = (b, h) if key == "all" else (0, 0)
+            x = src[name].clone()
+            at = {2: (bb, hh, dk // 3, dv - 5), 0: (bb, 75, hh)}[2 if name in ("h0", "dht") else 0]
+            if x.dim() == 4 and len(at) == 3:
+                at = at + (x.shape[3] - 5,)
+            x[at] = value
+            planted[key] = training_step(G, to_dev(dict(src, **{name: x})))
+        for n in clean:
+            kept = planted["one"][n] == clean1[n]
+            same = planted["all"][n] == clean[n]
+            unit = cut(same, n).reshape(kept.shape)
+            lost = int((kept & ~unit).sum())
+            assert lost == 0, (name, value, n, lost, int(kept.sum()))
+            if name in ("v", "dO") and n in ("o", "ht", "dv", "dh0"):
+                other = torch.arange(dv, device=unit.device) != dv - 5
+                assert bool(unit[..., other].all()), (name, value, n)
+            cut(same, n).fill_(True)
+            assert bool(same.all()), (name, value, n, "another unit changed")
