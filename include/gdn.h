@@ -98,7 +98,11 @@ size_t gdn_chunk_bwd_workspace_size(const gdn_problem *p);
  * (output mask read as the decay mask Gamma, with its diagonal).
  *   in : q, k, v, beta; log_alpha or NULL (alpha == 1); h0 = initial
  *        states or NULL (zero)
- *   out: o; ht = final states, or NULL to skip. */
+ *   out: o; ht = final states, or NULL to skip.
+ * o and ht may share memory with q, k and v, which they then overwrite (an
+ * input that the passes would still read is first copied into the workspace),
+ * and ht may be h0 (the state updated in place).  Other outputs, here and
+ * below, must not overlap a call's inputs unless its comment says so. */
 gdn_status gdn_chunk_fwd(const gdn_problem *p, const void *q, const void *k,
                          const void *v, const float *beta,
                          const float *log_alpha, const float *h0, void *o,

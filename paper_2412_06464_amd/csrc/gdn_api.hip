@@ -312,6 +312,7 @@ void fill_common(const gdn_problem* p, const Shape& s, Args* a) {
   a->N = s.N;
   a->NC = (int)s.NC;
   a->maxc = (int)s.maxc;
+  a->rows = s.Ttot * p->H;
   a->T = p->cu_seqlens ? 0 : p->T;
   a->cu = p->cu_seqlens;
 }

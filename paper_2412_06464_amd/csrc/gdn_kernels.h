@@ -14,6 +14,7 @@ struct Args {
   int NC;      // total chunks over all sequences
   int T;       // dense sequence length (used when cu == nullptr)
   int maxc;    // chunks of the longest sequence
+  long rows;   // rows of q, k, v and o: tokens x heads
   int gated;   // 0: alpha == 1 (no log_alpha input): g = 0, no gate math
   const int32_t* cu;  // packed boundaries [N+1] or nullptr (dense)
   // inputs

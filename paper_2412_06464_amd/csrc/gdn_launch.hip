@@ -1,6 +1,9 @@
 // Launch sequences of the forward and backward calls, with optional event
 // recording around every launch.
+#include <stdint.h>
 #include <string.h>
+
+#include <algorithm>
 
 #include "gdn_kernels.h"
 
@@ -125,11 +128,50 @@ static Args block_rule_inputs(Args a) {
   return a;
 }
 
+__global__ __launch_bounds__(256) void k_copy(const uint4* x, uint4* y, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
+    y[i] = x[i];
+}
+
+// The passes of gdn_chain.h read q, k and v while they write o and ht; those of
+// gdn_seq.hip have nothing of them left to read, their prep has it all.  So that
+// a call whose output lies over an input gives the same with either, an input
+// that shares memory with an output is read from a copy in the workspace.  v
+// in o's own place needs none: a wave has loaded a chunk's rows of its columns
+// before it stores that chunk's.
+static hipError_t chain_rule_inputs(Args& a, int dk, int dv, hipStream_t s, Timing* t) {
+  const size_t kb = (size_t)a.rows * dk * 2, vb = (size_t)a.rows * dv * 2;
+  const size_t hb = a.ht ? (size_t)a.N * a.H * dk * dv * 4 : 0;
+  auto apart = [](const void* x, size_t nx, const void* y, size_t ny) {
+    return (uintptr_t)x + nx <= (uintptr_t)y || (uintptr_t)y + ny <= (uintptr_t)x;
+  };
+  auto keep = [&](const void*& x, size_t n, void* copy) {
+    if ((apart(x, n, a.o, vb) || (&x == &a.v && x == a.o)) && apart(x, n, a.ht, hb))
+      return hipSuccess;
+    const void* src = x;
+    x = copy;
+    const size_t units = n / sizeof(uint4);
+    return timed(t, "k_copy", s, [&] {
+      hipLaunchKernelGGL(k_copy, dim3((unsigned)std::min<size_t>((units + 255) / 256, 4096)),
+                         dim3(256), 0, s, (const uint4*)src, (uint4*)copy, units);
+      return hipGetLastError();
+    });
+  };
+  hipError_t e = keep(a.v, vb, a.Uc);
+  if (e == hipSuccess) e = keep(a.q, kb, a.Qf);
+  if (e == hipSuccess) e = keep(a.k, kb, a.KbT);
+  return e;
+}
+
 hipError_t launch_fwd(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timing* t,
                       bool block) {
   if (audit(block ? Seq::BlockFwd : Seq::Fwd, in) >= 0) return hipErrorInvalidValue;
-  const Args a = block && use_chain(dt, dk, in) ? block_rule_inputs(in) : in;
   hipError_t e;
+  Args a = in;
+  if (use_chain(dt, dk, in)) {
+    if (block) a = block_rule_inputs(in);
+    else if ((e = chain_rule_inputs(a, dk, dv, s, t)) != hipSuccess) return e;
+  }
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
@@ -164,8 +206,12 @@ hipError_t launch_bwd(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timin
 hipError_t launch_fwd_save(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timing* t,
                            bool block) {
   if (audit(block ? Seq::BlockFwdSave : Seq::FwdSave, in) >= 0) return hipErrorInvalidValue;
-  const Args a = block && use_chain(dt, dk, in) ? block_rule_inputs(in) : in;
   hipError_t e;
+  Args a = in;
+  if (use_chain(dt, dk, in)) {
+    if (block) a = block_rule_inputs(in);
+    else if ((e = chain_rule_inputs(a, dk, dv, s, t)) != hipSuccess) return e;
+  }
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)

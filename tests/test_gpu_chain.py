@@ -106,3 +106,44 @@ def test_nonfinite_values_reach_no_further(G, dk, dv, B, H, T):
                 assert bool(unit[..., other].all()), (name, value, n)
             cut(same, n).fill_(True)
             assert bool(same.all()), (name, value, n, "another unit changed")
+
+
+@pytest.mark.parametrize("dk,dv,H", [(64, 64, 104), (128, 128, 60), (128, 128, 176),
+                                     (256, 512, 12)])
+@pytest.mark.parametrize("over", ["q", "k", "v", "all", "v_shifted", "ht_v"])
+def test_outputs_over_inputs(G, dk, dv, H, over):
+    """A forward whose outputs share memory with its inputs gives what it gives
+    with buffers of its own: o in the place of q, k, v or one tensor that is
+    all three, o on v's rows moved by 64 tokens, ht on v.  The passes read q, k
+    and v while they write o and ht, other sequence-heads' and later chunks'
+    among them."""
+    if over in ("q", "k", "all") and dk != dv:
+        pytest.skip("o has v's rows, not q's")
+    T = 300
+    d = to_dev(problem(dk, dv, 1, H, T, seed=34, h0_std=0.05))
+    say("over", dk, dv, H, over)
+    if over == "all":
+        d["k"] = d["q"] = d["v"] = d["k"]
+    elif over == "v_shifted":
+        room = torch.empty((1, T + 64, H, dv), dtype=d["v"].dtype, device="cuda")
+        d["v"] = room[:, :T].copy_(d["v"])
+    elif over == "ht_v":  # v's bytes inside a buffer that holds ht
+        n = max(d["v"].numel() * 2, H * dk * dv * 4)
+        room = torch.empty(n, dtype=torch.uint8, device="cuda")
+        d["v"] = room[:d["v"].numel() * 2].view(d["v"].dtype).view_as(d["v"]).copy_(d["v"])
+    want_o, want_ht = run_fwd(G, d)
+    keep = {n: d[n].clone() for n in ("q", "k", "v")}
+    for save in (False, True):
+        for n, x in keep.items():
+            d[n].copy_(x)
+        kw = dict(h0=d["h0"])
+        if over == "v_shifted":
+            kw["o"] = room[:, 64:]
+        elif over == "ht_v":
+            kw["ht"] = room[:H * dk * dv * 4].view(torch.float32).view(1, H, dk, dv)
+        else:
+            kw["o"] = d["v" if over == "all" else over]
+        args = (d["q"], d["k"], d["v"], d["beta"], d["log_alpha"])
+        o, ht = (G.gdn_chunk_fwd_save(*args, **kw)[:2] if save else G.gdn_chunk_fwd(*args, **kw))
+        torch.cuda.synchronize()
+        assert torch.equal(o, want_o) and torch.equal(ht, want_ht), (over, save)
