@@ -175,6 +175,49 @@ __device__ __forceinline__ void invert_unit_lower(const float* sA, float* sTf, f
   lds_barrier();
 }
 
+// What the passes of gdn_chain.h take from the prep, from this wave's 16 rows of
+// K K^T, Q K^T and K Q^T in accumulators (kq where MODE needs P, qk where it
+// needs P^T): P, P^T and Ak^T straight from there, then T diag(b) and T^T.  sg,
+// sb: g and beta.  sA, sTf, sYb: as for the inverse; every thread is past its
+// last read of whatever lay there.
+template <int MODE>
+__device__ __forceinline__ void small_operands(const Args& a, size_t ch, f32x4 (&kk)[1][4],
+                                               f32x4 (&qk)[1][4], f32x4 (&kq)[1][4],
+                                               const float* sg, const float* sb, float* sA,
+                                               float* sTf, float* sYb) {
+  using E = bf16;
+  constexpr bool FOUT = MODE != PREP_BWD, BOUT = MODE != PREP_FWD;
+  constexpr int LDA = CH + 1;
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = w * 16 + acc_row(e), i = j * 16 + acc_col();
+      // select, never multiply by an overflowed exp above the diagonal
+      const float dn = __expf(i <= r ? sg[r] - sg[i] : 0.f);  // Gamma_ri
+      const float up = __expf(r <= i ? sg[i] - sg[r] : 0.f);  // Gamma_ir
+      kk[0][j][e] = i < r ? dn * kk[0][j][e] : 0.f;
+      qk[0][j][e] = i <= r ? dn * qk[0][j][e] : 0.f;
+      kq[0][j][e] = r <= i ? up * kq[0][j][e] : 0.f;
+      sA[r * LDA + i] = sb[r] * kk[0][j][e];
+    }
+    if (BOUT) {
+      afrag_put_T<E>((E*)a.Ak + ch * CH * CH, CH, j, w, kk[0][j]);
+      afrag_put_T<E>((E*)a.PTf + ch * CH * CH, CH, j, w, qk[0][j]);
+    }
+    if (FOUT) afrag_put_T<E>((E*)a.Pf + ch * CH * CH, CH, j, w, kq[0][j]);
+  }
+  lds_barrier();
+  invert_unit_lower<LDA>(sA, sTf, sYb);
+  auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
+  export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
+                                    [&](int t, int i) { return T_at(t, i) * sb[i]; });
+  if (BOUT)
+    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                      [&](int i, int t) { return T_at(t, i); });
+}
+
 // Grid (NC, H), 256 threads (4 waves).  LDS stays below 80 KB for bf16 so
 // that two workgroups share a CU: one streams while the other solves.
 
@@ -185,9 +228,15 @@ __device__ __forceinline__ void invert_unit_lower(const float* sA, float* sTf, f
 // SMALL (with BLK only; k_prep_small is the one without): ahead of the passes
 // of gdn_chain.h, which read q, k and v themselves: beside the rule's q, k and
 // v only the 64 x 64 matrices are written (T diag(b) and P, and for the
-// backward P^T, T^T and Ak^T).
+// backward P^T, T^T and Ak^T).  It lives by the phases' latency, like
+// k_prep_small, and takes that kernel's LDS plan (42, 45 and 55 KB at dk 64,
+// 128 and 256): three workgroups share a CU at dk <= 128 instead of the two of
+// the general plan, with which it held the plain fused forward back, us,
+// general prep and passes / two workgroups / three: 75.5 / 78.8 / 69.4
+// (48 x 1024, 128/128), 84.0 / 85.8 / 80.2 (64 x 1024), 71.9 / 73.0 / 67.7
+// (96 x 1024, 64/64), 1,324 / 1,218 / 1,073 (65,536 x 16 packed, 128/128).
 template <class E, int DK, int DV, int MODE, bool BLK = false, bool SMALL = false>
-__global__ __launch_bounds__(256, 2) void k_prep(Args a) {
+__global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a) {
   static_assert(BLK || !SMALL, "k_prep_small");
   using M = Mfma<E>;
   // operands of the forward pass (diag(e^g) Q, P), of the reverse pass and
@@ -197,13 +246,18 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   constexpr int LD = CH + PADE;  // rows of 64 elements
   constexpr int LDA = CH + 1;
   constexpr int NKC = CH / M::K;
-  __shared__ __align__(16) E sX[CH * LD];  // K slice (Gram), then K_s^T or (b V_s)^T
-  __shared__ __align__(16) E sY[CH * LD];  // Q slice (Gram), then Q_s^T (backward)
-  __shared__ __align__(16) E sT[CH * LD];  // T, row-major
-  __shared__ __align__(16) E sP[CH * LD];  // P, row-major
-  __shared__ float sA[CH * LDA];           // diag(b) A
-  __shared__ float sTf[CH * LDA];          // T in fp32
-  __shared__ float sYb[32 * 33];         // products of the block recursion
+  // SMALL: T and the products of the block recursion lie over the slices, the
+  // prologue's weights have their place
+  constexpr int STAGE = 2 * CH * LD * (int)sizeof(E), INV = (CH * LDA + 32 * 33) * 4;
+  __shared__ __align__(16) unsigned char sXY[SMALL && INV > STAGE ? INV : STAGE];
+  __shared__ __align__(16) E sT[SMALL ? 1 : CH * LD];  // T, row-major
+  __shared__ __align__(16) E sP[SMALL ? 1 : CH * LD];  // P, row-major
+  __shared__ float sA[CH * LDA];                       // diag(b) A
+  __shared__ __align__(16) float sInv[SMALL ? 4 * (2 * DK + DV) : CH * LDA + 32 * 33];
+  E* sX = (E*)sXY;       // K slice (Gram), then K_s^T or (b V_s)^T
+  E* sY = sX + CH * LD;  // Q slice (Gram), then Q_s^T (backward)
+  float* sTf = SMALL ? (float*)sXY : sInv;  // T in fp32
+  float* sYb = sTf + CH * LDA;              // products of the block recursion
   __shared__ float sg[CH], sb[CH], seg[CH], sdec[CH], sbeg[CH];
 
   const int c = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
@@ -284,23 +338,25 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
                   "staging and row sums must fit in A");
     E* sXs = reinterpret_cast<E*>(sA);                    // staged slice (A is not formed yet)
     float* sNrm = sA + (S::BYTES + 15) / 16 * 4;          // [4 waves][CH] row sums
-    // weights by lag of the q | k | v channels, in the fp32 T buffer, which
-    // the inverse does not use yet
-    float4* sWl = reinterpret_cast<float4*>(sTf);
-    static_assert((2 * DK + DV) * sizeof(float4) <= CH * LDA * sizeof(float),
-                  "weights must fit in T");
+    // weights by lag of the q | k | v channels, where T is formed later (SMALL:
+    // the slices' place is taken until then)
+    float4* sWl = reinterpret_cast<float4*>(sInv);
+    static_assert((2 * DK + DV) * sizeof(float4) <= sizeof(sInv), "weights must fit");
     pro_weights(sWl, a.cwq + (size_t)h * DK * a.cw, a.cw, DK, tid, 256);
     pro_weights(sWl + DK, a.cwk + (size_t)h * DK * a.cw, a.cw, DK, tid, 256);
     pro_weights(sWl + 2 * DK, a.cwv + (size_t)h * DV * a.cw, a.cw, DV, tid, 256);
     const int nprev = start > pro_seq_start(a, ci) ? 3 : 0;  // chunks start 64-aligned in a sequence
     // the chunk's rows of all three projections into L2 first, where the
-    // workgroups an XCD runs at once (two per CU, 32 CUs) keep theirs within
-    // its 4 MB L2: 64 x 67 rows x (2 dk + dv) x 2 bytes is 3.3 MB at 128/128
-    // (prep 1.29 -> 1.20 ms at 65,536 tokens x 16 heads) but 8.8 MB at
-    // 256/512, where the warmed lines are gone before they are read (0.54 ->
-    // 0.57 ms).  Their offsets from the first staged row fit 32 bits.
+    // workgroups an XCD runs at once (two per CU, three with SMALL at dk <=
+    // 128, 32 CUs) keep theirs within its 4 MB L2: 64 x 67 rows x (2 dk + dv) x 2
+    // bytes is 3.3 MB at 128/128 (prep 1.29 -> 1.20 ms at 65,536 tokens x 16
+    // heads) but 8.8 MB at 256/512, where the warmed lines are gone before they
+    // are read (0.54 -> 0.57 ms); 96 x is 4.9 MB at 128/128 (prep 39.2 us with
+    // the warm-up and 35.5 without at 48 x 1024, 663 and 671 at 65,536 tokens x
+    // 16 heads).  Their offsets from the first staged row fit 32 bits.
     __shared__ float sWarm[64];
-    constexpr bool WARM = 64 * (CH + 3) * (2 * DK + DV) * (int)sizeof(E) <= (4 << 20);
+    constexpr int WGS = 32 * (SMALL && DK <= 128 ? 3 : 2);
+    constexpr bool WARM = WGS * (CH + 3) * (2 * DK + DV) * (int)sizeof(E) <= (4 << 20);
     if (WARM && (size_t)(CH + 3) * H * DV * sizeof(E) < (1u << 31)) {
       pro_warm((const E*)a.xq, DK, H, h, start, len, nprev, sWarm, tid, 256);
       pro_warm((const E*)a.xk, DK, H, h, start, len, nprev, sWarm, tid, 256);
@@ -421,9 +477,10 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
 
   // ---- Gram blocks K K^T and Q K^T over 64-wide slices of dk; wave w owns
   // rows 16w..16w+15.
-  f32x4 kk[1][4], qk[1][4];
+  f32x4 kk[1][4], qk[1][4], kq[1][4];
   zero_acc(kk);
   zero_acc(qk);
+  zero_acc(kq);
   static_for<0, KS>([&](auto sc) {
     constexpr int s = decltype(sc)::value;
     put_rows(sX, rk[s]);
@@ -434,7 +491,8 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
       if (a.yq) rows_out(sY, a.yq, DK, 64 * s);
     }
     wave_mma_nt<E, 1, 4, 64>(kk, sX + w * 16 * LD, LD, sX, LD);
-    wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
+    if (BOUT || !SMALL) wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
+    if constexpr (SMALL) wave_mma_nt<E, 1, 4, 64>(kq, sX + w * 16 * LD, LD, sY, LD);
     if (FOUT && !SMALL) {
       // diag(e^g) Q as A operands (rows t, k = d) for the output of the forward pass
       export_afrag_perm_kslice<E, CH, DK, 64, 256>(
@@ -447,6 +505,10 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
     }
     lds_barrier();
   });
+  if constexpr (SMALL) {
+    small_operands<MODE>(a, ch, kk, qk, kq, sg, sb, sA, sTf, sYb);
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -472,19 +534,11 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   invert_unit_lower<LDA>(sA, sTf, sYb);
   // T (zero above the diagonal blocks, where the buffer holds none)
   auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
-  if constexpr (SMALL) {
-    export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
-                                      [&](int t, int i) { return T_at(t, i) * sb[i]; });
-    if (BOUT)
-      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
-                                        [&](int i, int t) { return T_at(t, i); });
-  } else {
-    for (int idx = tid; idx < CH * CH; idx += 256) {
-      const int r = idx >> 6, i = idx & 63;
-      sT[r * LD + i] = to_e<E>(T_at(r, i));
-    }
-    lds_barrier();
+  for (int idx = tid; idx < CH * CH; idx += 256) {
+    const int r = idx >> 6, i = idx & 63;
+    sT[r * LD + i] = to_e<E>(T_at(r, i));
   }
+  lds_barrier();
 
   // ---- 64 x 64 operands
   if (FOUT) {
@@ -494,11 +548,9 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   if (BOUT) {
     export_afrag_perm<E, CH, CH, 256>((E*)a.PTf + ch * CH * CH,
                                       [&](int i, int t) { return to_f(sP[t * LD + i]); });
-    if (!SMALL)
-      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
-                                        [&](int i, int t) { return to_f(sT[t * LD + i]); });
+    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                      [&](int i, int t) { return to_f(sT[t * LD + i]); });
   }
-  if constexpr (SMALL) return;
 
   // ---- dk slices: W~ (and -W~^T), Kbar^T, (e^g Q)^T
   static_for<0, SMALL ? 0 : KS>([&](auto sc) {
@@ -570,13 +622,14 @@ __global__ __launch_bounds__(256, 2) void k_prep(Args a) {
   });
 }
 
-// The prep ahead of the passes of gdn_chain.h: g, T and P only (SMALL in
-// k_prep; with the block prologue that kernel does it).  Bound by the latency
+// The prep ahead of the passes of gdn_chain.h: g, T and P only (with the block
+// prologue: SMALL in k_prep).  Bound by the latency
 // of its phases (loads, Gram products, the inverse, stores), so its LDS is kept
-// at 39 KB and four workgroups share a CU: the inverse lies where the staged
+// at 38 KB and four workgroups share a CU (at dk = 256 too, whose 122 registers
+// the bound of three only keeps from spilling): the inverse lies where the staged
 // slices were, P and its transpose go out straight from accumulators (P from
 // K Q^T), and rows are loaded eight lanes to 128 bytes, not one lane to a row.
-// Against k_prep (two workgroups a CU, a lane to a row), bf16, us: forward
+// Against k_prep (two workgroups a CU, a lane to a row), bf16, warm, us: forward
 // 96 -> 55 (8 x 4096 x 6 heads, 256/512; 245 MB, 4.5 TB/s), 41 -> 30 (4 x 2048
 // x 16, 128/128), 132 -> 80 (8 x 4096 x 16, 64/64); saving pass 105 -> 82 (the
 // first), 415 -> 370 (65,536 x 16, 128/128, packed; 1.19 GB, 3.2 TB/s).
@@ -645,33 +698,7 @@ __global__ __launch_bounds__(256, DK > 128 ? 3 : 4) void k_prep_small(Args a) {
     if (BOUT) wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
     if (FOUT) wave_mma_nt<E, 1, 4, 64>(kq, sX + w * 16 * LD, LD, sY, LD);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = w * 16 + acc_row(e), i = j * 16 + acc_col();
-      // select, never multiply by an overflowed exp above the diagonal
-      const float dn = __expf(i <= r ? sg[r] - sg[i] : 0.f);  // Gamma_ri
-      const float up = __expf(r <= i ? sg[i] - sg[r] : 0.f);  // Gamma_ir
-      kk[0][j][e] = i < r ? dn * kk[0][j][e] : 0.f;
-      qk[0][j][e] = i <= r ? dn * qk[0][j][e] : 0.f;
-      kq[0][j][e] = r <= i ? up * kq[0][j][e] : 0.f;
-      sA[r * LDA + i] = sb[r] * kk[0][j][e];
-    }
-    if (BOUT) {
-      afrag_put_T<E>((E*)a.Ak + ch * CH * CH, CH, j, w, kk[0][j]);
-      afrag_put_T<E>((E*)a.PTf + ch * CH * CH, CH, j, w, qk[0][j]);
-    }
-    if (FOUT) afrag_put_T<E>((E*)a.Pf + ch * CH * CH, CH, j, w, kq[0][j]);
-  }
-  lds_barrier();
-  invert_unit_lower<LDA>(sA, sTf, sYb);
-  auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
-  export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
-                                    [&](int t, int i) { return T_at(t, i) * sb[i]; });
-  if (BOUT)
-    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
-                                      [&](int i, int t) { return T_at(t, i); });
+  small_operands<MODE>(a, ch, kk, qk, kq, sg, sb, sA, sTf, sYb);
 }
 
 // ------------------------------------------------------------------ launchers
