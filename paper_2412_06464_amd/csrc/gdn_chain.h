@@ -1106,19 +1106,32 @@ hipError_t bwd(const Args& a, hipStream_t s) {
 //    64/64: 123 / 123 at 64, 154 / 147 at 96.  (The plain forward at 256/512
 //    would gain from 6 units on, 123 / 105; it follows the same rule, so that
 //    it and the saving forward of a problem agree bit for bit);
-//  - 256/512: four waves of 16 columns up to one round of 8 workgroups per
-//    unit, then four of 32 (forward 129 / 167 at 32 units, 214 / 175 at 40);
-//  - 128/128: four waves of 16 columns while two workgroups per unit fill the
-//    chip once, then all 128 columns in one workgroup (training step 277 / 309
-//    at 128 units, 446 / 428 at 192; packed with eff 147: 2,744 / 3,009).
+//  - 256/512: four waves of 16 columns, 8 workgroups per unit, then four of
+//    32.  A CU holds one workgroup of either, so units of one length fill the chip once
+//    with 32 of them and a 33rd starts a second round (T = 1,024, training
+//    step 265 / 309 at 32 units, 389 / 333 at 33; forward 66 / 86 and 109 / 88).
+//    Units of different lengths make no rounds: the line lies where eff keeps
+//    the chip busy with 4 workgroups per unit (packed, forward 298 / 321 at
+//    eff 32, 154 / 152 at 39, 213 / 193 at 45, 180 / 170 at 51);
+//  - 128/128: the same with two workgroups per unit, then all 128 columns in
+//    one of eight waves.  One length: 128 units (training step 275 / 306 at 128,
+//    351 / 313 at 129, 394 / 358 at 160).  Different lengths: packed, training
+//    step 1,366 / 1,494 at eff 82, 2,686 / 2,907 at 93, 912 / 967 at 126, 2,425 /
+//    2,474 at 198.
+// The shapes of one (dk, dv) form the same sums in the same order: results do
+// not depend on which of them runs, only on whether these passes or those of
+// gdn_seq.hip do.
 namespace {
 struct ChainShape {
   int nc, nw;  // nw == 0: the passes of gdn_seq.hip
 };
 ChainShape chain_shape(int dk, const Args& a) {
   const long eff = (long)a.NC * a.H / (a.maxc > 0 ? a.maxc : 1);
-  if (dk == 256) return eff < 10 ? ChainShape{0, 0} : eff <= 36 ? ChainShape{1, 4} : ChainShape{2, 4};
-  if (dk == 128) return eff < 48 ? ChainShape{0, 0} : eff <= 160 ? ChainShape{1, 4} : ChainShape{1, 8};
+  const bool even = (long)a.N * a.maxc == a.NC;  // every sequence has as many chunks
+  if (dk == 256)
+    return eff < 10 ? ChainShape{0, 0} : eff <= (even ? 32 : 36) ? ChainShape{1, 4} : ChainShape{2, 4};
+  if (dk == 128)
+    return eff < 48 ? ChainShape{0, 0} : eff <= (even ? 128 : 160) ? ChainShape{1, 4} : ChainShape{1, 8};
   return eff < 96 ? ChainShape{0, 0} : ChainShape{1, 4};
 }
 }  // namespace

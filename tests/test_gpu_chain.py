@@ -147,3 +147,27 @@ def test_outputs_over_inputs(G, dk, dv, H, over):
         o, ht = (G.gdn_chunk_fwd_save(*args, **kw)[:2] if save else G.gdn_chunk_fwd(*args, **kw))
         torch.cuda.synchronize()
         assert torch.equal(o, want_o) and torch.equal(ht, want_ht), (over, save)
+
+
+@pytest.mark.parametrize("dk,dv,H,last", [(256, 512, 32, 1), (256, 512, 32, 4), (128, 128, 128, 1),
+                                          (128, 128, 128, 32)])
+def test_shapes_agree_around_their_line(G, dk, dv, H, last):
+    """One sequence with as many heads as fill the chip once, and the same
+    heads beside ``last`` more of them: the passes of other shapes, the same
+    bits.  Also packed, where the lines lie elsewhere: a short second sequence."""
+    T = 330
+    inp = problem(dk, dv, 1, H + last, T, seed=35, h0_std=0.05, backward=True)
+    few = {n: x[:, :H].contiguous() if n in ("h0", "dht") else x[:, :, :H].contiguous()
+           for n, x in inp.items() if isinstance(x, torch.Tensor)}
+    say("line", dk, dv, H, last)
+    one, more = training_step(G, to_dev(few)), training_step(G, to_dev(inp))
+    cu = torch.tensor([0, 200, T], dtype=torch.int32)
+    pack = dict(few, cu_seqlens=cu, h0=few["h0"].repeat(2, 1, 1, 1), dht=few["dht"].repeat(2, 1, 1, 1))
+    for n in one:
+        cut = more[n][:, :H] if n in ("ht", "dh0") else more[n][:, :, :H]
+        assert torch.equal(one[n], cut), n
+    packed = training_step(G, to_dev(pack))
+    alone = G.gdn_chunk_fwd(*(to_dev(few)[n][:, :200].contiguous()
+                              for n in ("q", "k", "v", "beta", "log_alpha")), h0=few["h0"].cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(packed["o"][:, :200], alone[0]) and torch.equal(packed["ht"][:1], alone[1])
