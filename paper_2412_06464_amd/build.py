@@ -14,20 +14,16 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgdn.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
-SOURCES = ["gdn_prep.hip", "gdn_seq.hip", "gdn_chain.hip", "gdn_grad.hip", "gdn_recurrent.hip",
-           "gdn_block.hip", "gdn_launch.hip", "gdn_api.hip"]
+SOURCES = ["gdn_prep.hip", "gdn_seq.hip", "gdn_grad.hip", "gdn_recurrent.hip", "gdn_block.hip",
+           "gdn_launch.hip", "gdn_api.hip"]
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++20", "-fPIC",
          # keep the compiler from emitting packed fp32 math
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# Extra flags of single sources: results of matrix instructions in vector
-# registers, also where a kernel may use all 512 of a lane.  The chain passes
-# scale their accumulators with vector instructions in every chunk; without it,
-# a fourth of the instructions of their loop are moves.  Of the general passes
-# it serves the fp32 ones at 256/512 (us, without / with it: forward 321 / 315 at
-# 1 x 1000 x 4 and 646 / 634 at 2 x 2048 x 6, training step 1,389 / 1,373), the
-# others are the same with and without.
-_MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-SOURCE_FLAGS = {"gdn_chain.hip": _MFMA_VGPR, "gdn_seq.hip": _MFMA_VGPR}
+# Extra flags of single sources.  The state passes scale their accumulators
+# with vector instructions in every chunk: results of matrix instructions in
+# vector registers, also where a kernel may use all 512 of a lane (gdn_chain.h;
+# without it, a fourth of the instructions of its loop are moves).
+SOURCE_FLAGS = {"gdn_seq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str, obj: str, extra=()) -> None:

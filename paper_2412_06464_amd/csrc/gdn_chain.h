@@ -40,6 +40,7 @@
 // gradients that the copy enters.  v and dO, whose columns stay apart through
 // the whole recurrence, are turned by transposed LDS reads instead, which
 // move values and keep a non-finite one in its column.
+#pragma once
 #include "gdn_device.h"
 #include "gdn_kernels.h"
 #include "gdn_seq_common.h"
@@ -49,7 +50,6 @@ namespace gdn {
 namespace {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
@@ -264,13 +264,14 @@ struct Cols {
   }
   // Transposed tiles (rows = the wave's columns, columns = the rows of row
   // tile i) to rows of a row-major matrix (base: the chunk's first row and
-  // head, stride rs bytes), through LDS (row_put, then row_out); or (frag_out)
-  // to fragment order over dv (tile: the row tile's first fragment).
+  // head, stride rs bytes), through LDS (row_put, then row_out); or (frag_out) to fragment order over
+  // dv (tile: the row tile's first fragment).
   template <class B>
   __device__ inline void row_put(const f32x4 (&t)[NC], const B& b) const {
     if constexpr (NC == 2) {
       B::put(b.op, __builtin_bit_cast(typename B::vec, pack8(t[0], t[1])));
     } else {
+      typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
       const bf16x4 x = {(bf16)t[0][0], (bf16)t[0][1], (bf16)t[0][2], (bf16)t[0][3]};
       B::put(b.op, __builtin_bit_cast(typename B::vec, x));
     }
@@ -287,6 +288,7 @@ struct Cols {
     if constexpr (NC == 2) {
       put_out<STREAM>((char*)f + l * 16u, pack8(t[0], t[1]));
     } else {
+      typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
       const bf16x4 x = {(bf16)t[0][0], (bf16)t[0][1], (bf16)t[0][2], (bf16)t[0][3]};
       f += ((v0 >> 4) & 1) * 256;
       put_out<STREAM>((char*)f + ((l & 15) * 16u + (g >> 1) * 256u + (g & 1) * 8u), x);
@@ -614,13 +616,13 @@ void k_fwd_chain(Args a) {
       // the next chunk's rows into the other buffer (its readers passed the
       // barrier), and the loads of the one after
       if constexpr (!AFTER) {
-        constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
-        rows.template store<X0, X1>(put);
-        load_rows(min(j + 2, nch - 1), int_c<X0>{}, int_c<X1>{});
-        if constexpr (kt == NKD - 1) {
-          tp.store(tri + step_tri, w);
-          load_tp(min(j + 2, nch - 1));
-        }
+      constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
+      rows.template store<X0, X1>(put);
+      load_rows(min(j + 2, nch - 1), int_c<X0>{}, int_c<X1>{});
+      if constexpr (kt == NKD - 1) {
+        tp.store(tri + step_tri, w);
+        load_tp(min(j + 2, nch - 1));
+      }
       }
       // K S
 #pragma unroll
@@ -912,13 +914,13 @@ void k_bwd_chain(Args a) {
       constexpr int kt = decltype(kc)::value;
       fetch(int_c<kt + D - 1>{});
       if constexpr (!AFTER) {
-        constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
-        rows.template store<X0, X1>(put);
-        load_rows(max(j - 2, 0), int_c<X0>{}, int_c<X1>{});
-        if constexpr (kt == NKD - 1) {
-          tp.store(tri + step_tri, w);
-          load_tp(max(j - 2, 0));
-        }
+      constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
+      rows.template store<X0, X1>(put);
+      load_rows(max(j - 2, 0), int_c<X0>{}, int_c<X1>{});
+      if constexpr (kt == NKD - 1) {
+        tp.store(tri + step_tri, w);
+        load_tp(max(j - 2, 0));
+      }
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)

@@ -29,7 +29,7 @@ struct Args {
   float* g;         // [ch][64]     cumulative log gate inside the chunk
   // workspace: per-chunk operands of the sequential passes (dtype E), as MFMA
   // A operands in fragment order with the permuted contraction order.  The
-  // passes of gdn_chain.hip read q, k and v themselves: of these they use Wf
+  // passes of gdn_chain.h read q, k and v themselves: of these they use Wf
   // (for T diag(b), 64 x 64), Pf, PTf and TTf only, and a fused forward that
   // is not asked for the rule's q, k and v keeps them in Qf, KbT and Uc.
   void* Wf;   // W~ = T diag(b e^g) K      rows t, k = d     64 x dk
@@ -143,7 +143,7 @@ hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStr
 hipError_t launch_bwd_seq(Dt dt, int dk, int dv, const Args& a, hipStream_t s);
 hipError_t launch_fwd_chain(int dk, int dv, int mode, const Args& a, hipStream_t s);
 hipError_t launch_bwd_chain(int dk, int dv, const Args& a, hipStream_t s);
-// Whether a call's state passes are those of gdn_chain.hip (bf16 with enough
+// Whether a call's state passes are those of gdn_chain.h (bf16 with enough
 // sequence-heads side by side) or those of gdn_seq.hip.  They read different
 // operands, so the prep follows it too.  The same for every call on a problem.
 bool use_chain(Dt dt, int dk, const Args& a);

@@ -115,7 +115,7 @@ Args audit_probe(uint64_t present) {
   return a;
 }
 
-// The fused block's forward ahead of the passes of gdn_chain.hip: the prep
+// The fused block's forward ahead of the passes of gdn_chain.h: the prep
 // writes the rule's q, k and v (to the caller's buffers, or to the workspace
 // where the caller wants none), the state pass reads them there.
 static Args block_rule_inputs(Args a) {
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void k_copy(const uint4* x, uint4* y, size_t n
     y[i] = x[i];
 }
 
-// The passes of gdn_chain.hip read q, k and v while they write o and ht; those of
+// The passes of gdn_chain.h read q, k and v while they write o and ht; those of
 // gdn_seq.hip have nothing of them left to read, their prep has it all.  So that
 // a call whose output lies over an input gives the same with either, an input
 // that shares memory with an output is read from a copy in the workspace.  v

@@ -24,7 +24,7 @@
 //                  for the reverse pass K, P^T, T^T, -W~^T, (e^g Q)^T, plus
 //                  strictLower(Gamma K K^T)^T for the gradient kernel.
 //                  Forward with save: both sets.
-//   k_prep_small   the same ahead of the bf16 passes of gdn_chain.hip, which read
+//   k_prep_small   the same ahead of the bf16 passes of gdn_chain.h, which read
 //                  q, k and v themselves: g, T diag(b) and P; for the backward
 //                  P^T, T^T and strictLower(Gamma K K^T)^T.
 #include "gdn_device.h"
@@ -175,7 +175,7 @@ __device__ __forceinline__ void invert_unit_lower(const float* sA, float* sTf, f
   lds_barrier();
 }
 
-// What the passes of gdn_chain.hip take from the prep, from this wave's 16 rows of
+// What the passes of gdn_chain.h take from the prep, from this wave's 16 rows of
 // K K^T, Q K^T and K Q^T in accumulators (kq where MODE needs P, qk where it
 // needs P^T): P, P^T and Ak^T straight from there, then T diag(b) and T^T.  sg,
 // sb: g and beta.  sA, sTf, sYb: as for the inverse; every thread is past its
@@ -226,7 +226,7 @@ __device__ __forceinline__ void small_operands(const Args& a, size_t ch, f32x4 (
 // and v are formed in registers from the projections a.xq, a.xk, a.xv (and
 // written to a.yq, a.yk, a.yv where those are set).
 // SMALL (with BLK only; k_prep_small is the one without): ahead of the passes
-// of gdn_chain.hip, which read q, k and v themselves: beside the rule's q, k and
+// of gdn_chain.h, which read q, k and v themselves: beside the rule's q, k and
 // v only the 64 x 64 matrices are written (T diag(b) and P, and for the
 // backward P^T, T^T and Ak^T).  It lives by the phases' latency, like
 // k_prep_small, and takes that kernel's LDS plan (42, 45 and 55 KB at dk 64,
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
   });
 }
 
-// The prep ahead of the passes of gdn_chain.hip: g, T and P only (with the block
+// The prep ahead of the passes of gdn_chain.h: g, T and P only (with the block
 // prologue: SMALL in k_prep).  Bound by the latency
 // of its phases (loads, Gram products, the inverse, stores), so its LDS is kept
 // at 38 KB and four workgroups share a CU (at dk = 256 too, whose 122 registers

@@ -1,8 +1,8 @@
 // Sequential inter-chunk state passes (gfx950) of the chunkwise gated delta
 // rule (Sec. 3.3; state stored dk x dv): in fp32, and in bf16 where few
-// sequence-heads run side by side (the others: gdn_chain.hip, and the rule
-// there).  One workgroup owns one (sequence, head, BV-wide slice of dv): the
-// dk x BV state tile lives in the MFMA accumulators of its four waves (wave w owns state rows [w dk/4, (w+1) dk/4))
+// sequence-heads run side by side (the others: gdn_chain.h, and the rule there).  One workgroup owns one (sequence,
+// head, BV-wide slice of dv): the dk x BV state tile lives in the MFMA
+// accumulators of its four waves (wave w owns state rows [w dk/4, (w+1) dk/4))
 // and the chunks of the sequence are walked in order.  Per chunk the state
 // (or its gradient) and the chunk's V' (or dV') are published to LDS as MFMA
 // B operands straight from the accumulators (permuted contraction order, one
@@ -19,6 +19,8 @@
 #include "gdn_device.h"
 #include "gdn_kernels.h"
 #include "gdn_seq_common.h"
+
+#include "gdn_chain.h"
 
 namespace gdn {
 
