@@ -50,6 +50,7 @@ namespace gdn {
 namespace {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
@@ -264,14 +265,13 @@ struct Cols {
   }
   // Transposed tiles (rows = the wave's columns, columns = the rows of row
   // tile i) to rows of a row-major matrix (base: the chunk's first row and
-  // head, stride rs bytes), through LDS (row_put, then row_out); or (frag_out) to fragment order over
-  // dv (tile: the row tile's first fragment).
+  // head, stride rs bytes), through LDS (row_put, then row_out); or (frag_out)
+  // to fragment order over dv (tile: the row tile's first fragment).
   template <class B>
   __device__ inline void row_put(const f32x4 (&t)[NC], const B& b) const {
     if constexpr (NC == 2) {
       B::put(b.op, __builtin_bit_cast(typename B::vec, pack8(t[0], t[1])));
     } else {
-      typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
       const bf16x4 x = {(bf16)t[0][0], (bf16)t[0][1], (bf16)t[0][2], (bf16)t[0][3]};
       B::put(b.op, __builtin_bit_cast(typename B::vec, x));
     }
@@ -288,7 +288,6 @@ struct Cols {
     if constexpr (NC == 2) {
       put_out<STREAM>((char*)f + l * 16u, pack8(t[0], t[1]));
     } else {
-      typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
       const bf16x4 x = {(bf16)t[0][0], (bf16)t[0][1], (bf16)t[0][2], (bf16)t[0][3]};
       f += ((v0 >> 4) & 1) * 256;
       put_out<STREAM>((char*)f + ((l & 15) * 16u + (g >> 1) * 256u + (g & 1) * 8u), x);
@@ -616,13 +615,13 @@ void k_fwd_chain(Args a) {
       // the next chunk's rows into the other buffer (its readers passed the
       // barrier), and the loads of the one after
       if constexpr (!AFTER) {
-      constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
-      rows.template store<X0, X1>(put);
-      load_rows(min(j + 2, nch - 1), int_c<X0>{}, int_c<X1>{});
-      if constexpr (kt == NKD - 1) {
-        tp.store(tri + step_tri, w);
-        load_tp(min(j + 2, nch - 1));
-      }
+        constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
+        rows.template store<X0, X1>(put);
+        load_rows(min(j + 2, nch - 1), int_c<X0>{}, int_c<X1>{});
+        if constexpr (kt == NKD - 1) {
+          tp.store(tri + step_tri, w);
+          load_tp(min(j + 2, nch - 1));
+        }
       }
       // K S
 #pragma unroll
@@ -914,13 +913,13 @@ void k_bwd_chain(Args a) {
       constexpr int kt = decltype(kc)::value;
       fetch(int_c<kt + D - 1>{});
       if constexpr (!AFTER) {
-      constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
-      rows.template store<X0, X1>(put);
-      load_rows(max(j - 2, 0), int_c<X0>{}, int_c<X1>{});
-      if constexpr (kt == NKD - 1) {
-        tp.store(tri + step_tri, w);
-        load_tp(max(j - 2, 0));
-      }
+        constexpr int X0 = kt * R::PER / NKD, X1 = (kt + 1) * R::PER / NKD;
+        rows.template store<X0, X1>(put);
+        load_rows(max(j - 2, 0), int_c<X0>{}, int_c<X1>{});
+        if constexpr (kt == NKD - 1) {
+          tp.store(tri + step_tri, w);
+          load_tp(max(j - 2, 0));
+        }
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -1073,96 +1072,6 @@ void k_bwd_chain(Args a) {
   }
 
   if (a.dh0) store_state<DV>(a.dh0 + sbase, dS);
-}
-
-// ------------------------------------------------------------------ launchers
-
-namespace {
-
-template <int DK, int DV, int MODE, int NC, int NW>
-hipError_t fwd(const Args& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_fwd_chain<DK, DV, MODE, NC, NW>),
-                     dim3(unit_tile_grid(DV / (16 * NC * NW), a.N * a.H)), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-template <int DK, int DV, int NC, int NW>
-hipError_t bwd(const Args& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_bwd_chain<DK, DV, NC, NW>),
-                     dim3(unit_tile_grid(DV / (16 * NC * NW), a.N * a.H)), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-
-}  // namespace
-
-// (dk, dv), 16-wide column tiles per wave and waves per workgroup.  Which of
-// them, and whether these passes or those of gdn_seq.hip, follows from the
-// chains that run side by side: eff, chunk-heads over the longest sequence's
-// chunks (units for sequences of one length).  All measured with the prep
-// kernel of each form, T = 2,048 at 256/512 and 1,024 below, microseconds:
-//  - few chains: a chunk's latency counts, and four waves that share a
-//    chunk's products (gdn_seq.hip) are quicker than four chains.  Training
-//    step at 256/512: 258 / 276 at 6 units, 325 / 320 at 12, 374 / 346 at 16,
-//    698 / 510 at 32; at 128/128: 135 / 136 at 32 units, 200 / 178 at 64; at
-//    64/64: 123 / 123 at 64, 154 / 147 at 96.  (The plain forward at 256/512
-//    would gain from 6 units on, 123 / 105; it follows the same rule, so that
-//    it and the saving forward of a problem agree bit for bit);
-//  - 256/512: four waves of 16 columns, 8 workgroups per unit, then four of
-//    32.  A CU holds one workgroup of either, so units of one length fill the chip once
-//    with 32 of them and a 33rd starts a second round (T = 1,024, training
-//    step 265 / 309 at 32 units, 389 / 333 at 33; forward 66 / 86 and 109 / 88).
-//    Units of different lengths make no rounds: the line lies where eff keeps
-//    the chip busy with 4 workgroups per unit (packed, forward 298 / 321 at
-//    eff 32, 154 / 152 at 39, 213 / 193 at 45, 180 / 170 at 51);
-//  - 128/128: the same with two workgroups per unit, then all 128 columns in
-//    one of eight waves.  One length: 128 units (training step 275 / 306 at 128,
-//    351 / 313 at 129, 394 / 358 at 160).  Different lengths: packed, training
-//    step 1,366 / 1,494 at eff 82, 2,686 / 2,907 at 93, 912 / 967 at 126, 2,425 /
-//    2,474 at 198.
-// The shapes of one (dk, dv) form the same sums in the same order: results do
-// not depend on which of them runs, only on whether these passes or those of
-// gdn_seq.hip do.
-namespace {
-struct ChainShape {
-  int nc, nw;  // nw == 0: the passes of gdn_seq.hip
-};
-ChainShape chain_shape(int dk, const Args& a) {
-  const long eff = (long)a.NC * a.H / (a.maxc > 0 ? a.maxc : 1);
-  const bool even = (long)a.N * a.maxc == a.NC;  // every sequence has as many chunks
-  if (dk == 256)
-    return eff < 10 ? ChainShape{0, 0} : eff <= (even ? 32 : 36) ? ChainShape{1, 4} : ChainShape{2, 4};
-  if (dk == 128)
-    return eff < 48 ? ChainShape{0, 0} : eff <= (even ? 128 : 160) ? ChainShape{1, 4} : ChainShape{1, 8};
-  return eff < 96 ? ChainShape{0, 0} : ChainShape{1, 4};
-}
-}  // namespace
-
-bool use_chain(Dt dt, int dk, const Args& a) {
-  return dt == Dt::BF16 && chain_shape(dk, a).nw != 0;
-}
-
-hipError_t launch_fwd_chain(int dk, int dv, int mode, const Args& a, hipStream_t s) {
-  const ChainShape c = chain_shape(dk, a);
-  auto f = [&]<int DK, int DV, int NC, int NW>() {
-    if (mode == SEQ_STORE) return fwd<DK, DV, SEQ_STORE, NC, NW>(a, s);
-    if (mode == SEQ_SAVE) return fwd<DK, DV, SEQ_SAVE, NC, NW>(a, s);
-    return fwd<DK, DV, SEQ_FWD, NC, NW>(a, s);
-  };
-  if (dk == 256 && dv == 512)
-    return c.nc == 2 ? f.template operator()<256, 512, 2, 4>()
-                     : f.template operator()<256, 512, 1, 4>();
-  if (dk == 128 && dv == 128)
-    return c.nw == 8 ? f.template operator()<128, 128, 1, 8>()
-                     : f.template operator()<128, 128, 1, 4>();
-  if (dk == 64 && dv == 64) return f.template operator()<64, 64, 1, 4>();
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_bwd_chain(int dk, int dv, const Args& a, hipStream_t s) {
-  const ChainShape c = chain_shape(dk, a);
-  if (dk == 256 && dv == 512) return c.nc == 2 ? bwd<256, 512, 2, 4>(a, s) : bwd<256, 512, 1, 4>(a, s);
-  if (dk == 128 && dv == 128) return c.nw == 8 ? bwd<128, 128, 1, 8>(a, s) : bwd<128, 128, 1, 4>(a, s);
-  if (dk == 64 && dv == 64) return bwd<64, 64, 1, 4>(a, s);
-  return hipErrorInvalidValue;
 }
 
 }  // namespace gdn

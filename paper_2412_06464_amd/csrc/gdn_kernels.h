@@ -141,8 +141,6 @@ hipError_t launch_prep(Dt dt, int dk, int dv, int mode, const Args& a, hipStream
                        bool block = false);
 hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStream_t s);
 hipError_t launch_bwd_seq(Dt dt, int dk, int dv, const Args& a, hipStream_t s);
-hipError_t launch_fwd_chain(int dk, int dv, int mode, const Args& a, hipStream_t s);
-hipError_t launch_bwd_chain(int dk, int dv, const Args& a, hipStream_t s);
 // Whether a call's state passes are those of gdn_chain.h (bf16 with enough
 // sequence-heads side by side) or those of gdn_seq.hip.  They read different
 // operands, so the prep follows it too.  The same for every call on a problem.

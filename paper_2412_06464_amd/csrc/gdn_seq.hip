@@ -1,8 +1,8 @@
 // Sequential inter-chunk state passes (gfx950) of the chunkwise gated delta
 // rule (Sec. 3.3; state stored dk x dv): in fp32, and in bf16 where few
-// sequence-heads run side by side (the others: gdn_chain.h, and the rule there).  One workgroup owns one (sequence,
-// head, BV-wide slice of dv): the dk x BV state tile lives in the MFMA
-// accumulators of its four waves (wave w owns state rows [w dk/4, (w+1) dk/4))
+// sequence-heads run side by side (the others: gdn_chain.h; the rule is at the
+// launchers below).  One workgroup owns one (sequence, head, BV-wide slice of
+// dv): the dk x BV state tile lives in the MFMA accumulators of its four waves (wave w owns state rows [w dk/4, (w+1) dk/4))
 // and the chunks of the sequence are walked in order.  Per chunk the state
 // (or its gradient) and the chunk's V' (or dV') are published to LDS as MFMA
 // B operands straight from the accumulators (permuted contraction order, one
@@ -19,11 +19,9 @@
 #include "gdn_device.h"
 #include "gdn_kernels.h"
 #include "gdn_seq_common.h"
-
 #include "gdn_chain.h"
 
 namespace gdn {
-
 
 // dv slice per workgroup and the workgroups per CU the register budget is
 // sized for.  The forward at dk = 256 takes 64-wide slices: every chunk moves
@@ -664,6 +662,91 @@ __global__ __launch_bounds__(256, GDN_SEQ_MINB) void k_bwd_seq(Args a) {
 }
 
 // ------------------------------------------------------------------ launchers
+
+namespace {
+
+template <int DK, int DV, int MODE, int NC, int NW>
+hipError_t fwd(const Args& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_fwd_chain<DK, DV, MODE, NC, NW>),
+                     dim3(unit_tile_grid(DV / (16 * NC * NW), a.N * a.H)), dim3(64 * NW), 0, s, a);
+  return hipGetLastError();
+}
+template <int DK, int DV, int NC, int NW>
+hipError_t bwd(const Args& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_bwd_chain<DK, DV, NC, NW>),
+                     dim3(unit_tile_grid(DV / (16 * NC * NW), a.N * a.H)), dim3(64 * NW), 0, s, a);
+  return hipGetLastError();
+}
+
+// The chain passes: 16-wide column tiles per wave and waves per workgroup.
+// Which of them, and whether these passes or the general ones, follows from the
+// chains that run side by side: eff, chunk-heads over the longest sequence's
+// chunks (units for sequences of one length).  All measured with the prep
+// kernel of each form, T = 2,048 at 256/512 and 1,024 below, microseconds:
+//  - few chains: a chunk's latency counts, and four waves that share a
+//    chunk's products are quicker than four chains.  Training
+//    step at 256/512: 258 / 276 at 6 units, 325 / 320 at 12, 374 / 346 at 16,
+//    698 / 510 at 32; at 128/128: 135 / 136 at 32 units, 200 / 178 at 64; at
+//    64/64: 123 / 123 at 64, 154 / 147 at 96.  (The plain forward at 256/512
+//    would gain from 6 units on, 123 / 105; it follows the same rule, so that
+//    it and the saving forward of a problem agree bit for bit);
+//  - 256/512: four waves of 16 columns, 8 workgroups per unit, then four of
+//    32.  A CU holds one workgroup of either, so 32 units of one length fill
+//    the chip once and a 33rd starts a second round (T = 1,024, training step
+//    265 / 309 at 32 units, 389 / 333 at 33; forward 66 / 86 and 109 / 88).
+//    Units of different lengths make no rounds: the line lies where eff keeps
+//    the chip busy with 4 workgroups per unit (packed, forward 298 / 321 at
+//    eff 32, 154 / 152 at 39, 213 / 193 at 45, 180 / 170 at 51);
+//  - 128/128: the same with two workgroups per unit, then all 128 columns in
+//    one of eight waves.  One length: 128 units (training step 275 / 306 at 128,
+//    351 / 313 at 129, 394 / 358 at 160).  Different lengths: packed, training
+//    step 1,366 / 1,494 at eff 82, 2,686 / 2,907 at 93, 912 / 967 at 126, 2,425 /
+//    2,474 at 198.
+// The shapes of one (dk, dv) form the same sums in the same order: results do
+// not depend on which of them runs, only on whether these passes or the general
+// ones do.
+struct ChainShape {
+  int nc, nw;  // nw == 0: the general passes
+};
+ChainShape chain_shape(int dk, const Args& a) {
+  const long eff = (long)a.NC * a.H / (a.maxc > 0 ? a.maxc : 1);
+  const bool even = (long)a.N * a.maxc == a.NC;  // every sequence has as many chunks
+  if (dk == 256)
+    return eff < 10 ? ChainShape{0, 0} : eff <= (even ? 32 : 36) ? ChainShape{1, 4} : ChainShape{2, 4};
+  if (dk == 128)
+    return eff < 48 ? ChainShape{0, 0} : eff <= (even ? 128 : 160) ? ChainShape{1, 4} : ChainShape{1, 8};
+  return eff < 96 ? ChainShape{0, 0} : ChainShape{1, 4};
+}
+}  // namespace
+
+bool use_chain(Dt dt, int dk, const Args& a) {
+  return dt == Dt::BF16 && chain_shape(dk, a).nw != 0;
+}
+
+static hipError_t launch_fwd_chain(int dk, int dv, int mode, const Args& a, hipStream_t s) {
+  const ChainShape c = chain_shape(dk, a);
+  auto f = [&]<int DK, int DV, int NC, int NW>() {
+    if (mode == SEQ_STORE) return fwd<DK, DV, SEQ_STORE, NC, NW>(a, s);
+    if (mode == SEQ_SAVE) return fwd<DK, DV, SEQ_SAVE, NC, NW>(a, s);
+    return fwd<DK, DV, SEQ_FWD, NC, NW>(a, s);
+  };
+  if (dk == 256 && dv == 512)
+    return c.nc == 2 ? f.template operator()<256, 512, 2, 4>()
+                     : f.template operator()<256, 512, 1, 4>();
+  if (dk == 128 && dv == 128)
+    return c.nw == 8 ? f.template operator()<128, 128, 1, 8>()
+                     : f.template operator()<128, 128, 1, 4>();
+  if (dk == 64 && dv == 64) return f.template operator()<64, 64, 1, 4>();
+  return hipErrorInvalidValue;
+}
+
+static hipError_t launch_bwd_chain(int dk, int dv, const Args& a, hipStream_t s) {
+  const ChainShape c = chain_shape(dk, a);
+  if (dk == 256 && dv == 512) return c.nc == 2 ? bwd<256, 512, 2, 4>(a, s) : bwd<256, 512, 1, 4>(a, s);
+  if (dk == 128 && dv == 128) return c.nw == 8 ? bwd<128, 128, 1, 8>(a, s) : bwd<128, 128, 1, 4>(a, s);
+  if (dk == 64 && dv == 64) return bwd<64, 64, 1, 4>(a, s);
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_fwd_seq(Dt dt, int dk, int dv, int mode, const Args& a, hipStream_t s) {
   if (use_chain(dt, dk, a)) return launch_fwd_chain(dk, dv, mode, a, s);
