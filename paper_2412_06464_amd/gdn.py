@@ -313,11 +313,16 @@ def gdn_status_string(code: int) -> str:
     return load_library().gdn_status_string(code).decode()
 
 
+# The handle of a device's current stream without a Stream object made for it,
+# where this torch has that (no public name).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
-    """The current stream of a device, as its handle (no Stream object made)."""
-    if device.type != "cuda" or device.index is None:
+    """The current stream of a device, as its handle."""
+    if _raw_stream is None or device.type != "cuda" or device.index is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return _raw_stream(device.index)
 
 
 def _check(code: int):
