@@ -106,7 +106,12 @@ def kernel_models(w, tokens_heads, n_units, has_h0):
     sum is the path's forward + backward FLOP.  The stateless backward's
     recompute launches are credited with the recompute they perform.
     Bytes: only the call's own tensors the kernel reads or writes (e = element
-    bytes; gates fp32; each state dk dv fp32 per (sequence, head))."""
+    bytes; gates fp32; each state dk dv fp32 per (sequence, head)).
+
+    The chain passes (bf16, many sequence-heads) divide the steps otherwise:
+    their prep forms no W~ and U~ (4 C dk + C^2/3; q, k and the gates in), the
+    passes read k, q and v (dO) themselves and multiply the residual by
+    T diag(b) (2 C dv more in the forward).  W~'s 2 C dk falls away."""
     e = 4 if w.dtype == "f32" else 2
     dk, dv, C = w.dk, w.dv, CH
     st = w.dk * w.dv * 4 * n_units
@@ -124,6 +129,15 @@ def kernel_models(w, tokens_heads, n_units, has_h0):
         "k_grad": ((4 * dk + 2 * dv) * e + 12, 6 * dk * dv + 12 * C * dk + 4 * C * dv + 4 * C * C,
                    0),
         "k_chunk_table": (0, 0, 0),
+        "k_copy": (0, 0, 0),
+        "k_prep_small": (2 * dk * e + 8, 4 * C * dk + C * C / 3, 0),
+        "k_prep_small_save": (2 * dk * e + 8, 4 * C * dk + C * C / 3, 0),
+        "k_fwd_chain": ((2 * dk + 2 * dv) * e, 6 * dk * dv + 4 * C * dv,
+                        st * (2 if has_h0 else 1)),
+        "k_fwd_chain_save": ((2 * dk + 2 * dv) * e, 6 * dk * dv + 4 * C * dv,
+                             st * (2 if has_h0 else 1)),
+        "k_fwd_chain_store": ((dk + dv) * e, 4 * dk * dv + 2 * C * dv, st if has_h0 else 0),
+        "k_bwd_chain": ((2 * dk + 2 * dv) * e + 4, 6 * dk * dv + 4 * C * dv, 2 * st),
     }
     return {k: (b * tokens_heads + s, f * tokens_heads) for k, (b, f, s) in per.items()}
 
@@ -500,6 +514,13 @@ def fused_models(w, tokens_heads, n_units, has_h0):
     m = kernel_models(w, tokens_heads, n_units, has_h0)
     m["k_prep_save_block"] = m["k_prep_save"]
     m["k_prep_block"] = m["k_prep"]
+    # ahead of the chain passes it reads the projections just the same, and the
+    # rule's q, k, v that it writes are intermediates
+    m["k_prep_small_save_block"] = (m["k_prep"][0], m["k_prep_small"][1])
+    m["k_prep_small_block"] = m["k_prep_small_save_block"]
+    for name in ("k_fwd_chain", "k_fwd_chain_save"):
+        m[name] = (m[name.replace("chain", "seq")][0], m[name][1])
+    m["k_bwd_chain"] = (m["k_bwd_seq"][0], m["k_bwd_chain"][1])
     m["k_grad_block"] = m["k_grad"]
     m["k_block_fixup"] = (0, 0)
     m["k_conv_bwd"] = (2 * w.dv * 2 * tokens_heads, 0)
@@ -643,9 +664,9 @@ def bench_fused_block(args):
         roof = {"bound": "mfma", "achieved": kf / t_dom / 1e12, "peak": PEAK_MFMA_BF16 / 1e12,
                 "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    from paper_2412_06464_amd.profiling import block_kernel_key, kernel_key
+    from paper_2412_06464_amd.profiling import block_kernel_key, find_kernel, kernel_key
     counters, step_counter = traffic_record(args.workload)
-    tr = counters.get(kernel_key(dom, "bf16", dk, dv))
+    tr = find_kernel(counters, kernel_key(dom, "bf16", dk, dv))
     roof["traffic"] = tr
     roof["traffic_ratio"] = tr / kb if tr and kb else None
     roof.update(kernel=dom, kernel_ms=kern_ms[dom], algorithmic_gbytes=kb / 1e9,
@@ -856,11 +877,11 @@ def main():
         roof = {"bound": cbound, "achieved": kf / t_dom / 1e12, "peak": peak_c / 1e12,
                 "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    from paper_2412_06464_amd.profiling import kernel_key
+    from paper_2412_06464_amd.profiling import find_kernel, kernel_key
     counters, step_counter = traffic_record(args.workload)
     if path != ("saved" if w.backward else path):
         step_counter = None  # the counters are taken on the headline path
-    tr = counters.get(kernel_key(dom, w.dtype, w.dk, w.dv))
+    tr = find_kernel(counters, kernel_key(dom, w.dtype, w.dk, w.dv))
     roof["traffic"] = tr
     roof["traffic_ratio"] = tr / kb if tr and kb else None
     roof.update(kernel=dom, kernel_ms=kern_ms[dom], algorithmic_gbytes=kb / 1e9,

@@ -316,7 +316,8 @@ gdn_status gdn_block_bwd_saved(const gdn_problem *p,
  * *_timed call records events[2i] just before and events[2i+1] just after
  * its i-th kernel launch on `stream`, for the first capacity/2 launches, and
  * reports how many launches it made and their kernel names (static strings
- * owned by the library).  Durations are read with hipEventElapsedTime once
+ * owned by the library; a name tells the kernel's mode and form, not its
+ * template arguments).  Durations are read with hipEventElapsedTime once
  * the stream has passed the events.  With timing == NULL a *_timed call is
  * exactly the plain call.  Same arguments, checks and statuses otherwise. */
 typedef struct {

@@ -27,6 +27,22 @@ hipError_t timed(Timing* t, const char* name, hipStream_t s, F&& launch) {
   return hipSuccess;
 }
 
+// Names of the launches in the timing record: what the prep and the state passes
+// are called depends on which of the two forms runs.
+struct Names {
+  bool chain;
+  const char* prep() const { return chain ? "k_prep_small" : "k_prep"; }
+  const char* prep_save() const { return chain ? "k_prep_small_save" : "k_prep_save"; }
+  const char* prep_block() const { return chain ? "k_prep_small_block" : "k_prep_block"; }
+  const char* prep_save_block() const {
+    return chain ? "k_prep_small_save_block" : "k_prep_save_block";
+  }
+  const char* fwd() const { return chain ? "k_fwd_chain" : "k_fwd_seq"; }
+  const char* fwd_store() const { return chain ? "k_fwd_chain_store" : "k_fwd_seq_store"; }
+  const char* fwd_save() const { return chain ? "k_fwd_chain_save" : "k_fwd_seq_save"; }
+  const char* bwd() const { return chain ? "k_bwd_chain" : "k_bwd_seq"; }
+};
+
 // Pointer fields of Args, in audit order.
 #define GDN_AUDIT_FIELDS(X)                                                                    \
   X(q) X(k) X(v) X(beta) X(log_alpha) X(h0) X(dO) X(dht) X(o) X(ht) X(dq) X(dk) X(dv) X(dbeta) \
@@ -168,7 +184,8 @@ hipError_t launch_fwd(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timi
   if (audit(block ? Seq::BlockFwd : Seq::Fwd, in) >= 0) return hipErrorInvalidValue;
   hipError_t e;
   Args a = in;
-  if (use_chain(dt, dk, in)) {
+  const Names name{use_chain(dt, dk, in)};
+  if (name.chain) {
     if (block) a = block_rule_inputs(in);
     else if ((e = chain_rule_inputs(a, dk, dv, s, t)) != hipSuccess) return e;
   }
@@ -176,26 +193,27 @@ hipError_t launch_fwd(Dt dt, int dk, int dv, const Args& in, hipStream_t s, Timi
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
     return e;
-  if ((e = timed(t, block ? "k_prep_block" : "k_prep", s,
+  if ((e = timed(t, block ? name.prep_block() : name.prep(), s,
                  [&] { return launch_prep(dt, dk, dv, PREP_FWD, a, s, block); })) != hipSuccess)
     return e;
-  return timed(t, "k_fwd_seq", s, [&] { return launch_fwd_seq(dt, dk, dv, SEQ_FWD, a, s); });
+  return timed(t, name.fwd(), s, [&] { return launch_fwd_seq(dt, dk, dv, SEQ_FWD, a, s); });
 }
 
 hipError_t launch_bwd(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timing* t) {
   if (audit(Seq::Bwd, a) >= 0) return hipErrorInvalidValue;
+  const Names name{use_chain(dt, dk, a)};
   hipError_t e;
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
     return e;
-  if ((e = timed(t, "k_prep", s, [&] { return launch_prep(dt, dk, dv, PREP_BWD, a, s); })) !=
+  if ((e = timed(t, name.prep(), s, [&] { return launch_prep(dt, dk, dv, PREP_BWD, a, s); })) !=
       hipSuccess)
     return e;
-  if ((e = timed(t, "k_fwd_seq_store", s,
+  if ((e = timed(t, name.fwd_store(), s,
                  [&] { return launch_fwd_seq(dt, dk, dv, SEQ_STORE, a, s); })) != hipSuccess)
     return e;
-  if ((e = timed(t, "k_bwd_seq", s, [&] { return launch_bwd_seq(dt, dk, dv, a, s); })) !=
+  if ((e = timed(t, name.bwd(), s, [&] { return launch_bwd_seq(dt, dk, dv, a, s); })) !=
       hipSuccess)
     return e;
   return timed(t, "k_grad", s, [&] { return launch_grad(dt, dk, dv, a, s); });
@@ -208,7 +226,8 @@ hipError_t launch_fwd_save(Dt dt, int dk, int dv, const Args& in, hipStream_t s,
   if (audit(block ? Seq::BlockFwdSave : Seq::FwdSave, in) >= 0) return hipErrorInvalidValue;
   hipError_t e;
   Args a = in;
-  if (use_chain(dt, dk, in)) {
+  const Names name{use_chain(dt, dk, in)};
+  if (name.chain) {
     if (block) a = block_rule_inputs(in);
     else if ((e = chain_rule_inputs(a, dk, dv, s, t)) != hipSuccess) return e;
   }
@@ -216,22 +235,23 @@ hipError_t launch_fwd_save(Dt dt, int dk, int dv, const Args& in, hipStream_t s,
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
     return e;
-  if ((e = timed(t, block ? "k_prep_save_block" : "k_prep_save", s,
+  if ((e = timed(t, block ? name.prep_save_block() : name.prep_save(), s,
                  [&] { return launch_prep(dt, dk, dv, PREP_SAVE, a, s, block); })) != hipSuccess)
     return e;
-  return timed(t, "k_fwd_seq_save", s,
+  return timed(t, name.fwd_save(), s,
                [&] { return launch_fwd_seq(dt, dk, dv, SEQ_SAVE, a, s); });
 }
 
 // Backward from a saving forward's buffer: no prep, no recompute.
 hipError_t launch_bwd_saved(Dt dt, int dk, int dv, const Args& a, hipStream_t s, Timing* t) {
   if (audit(Seq::BwdSaved, a) >= 0) return hipErrorInvalidValue;
+  const Names name{use_chain(dt, dk, a)};
   hipError_t e;
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
     return e;
-  if ((e = timed(t, "k_bwd_seq", s, [&] { return launch_bwd_seq(dt, dk, dv, a, s); })) !=
+  if ((e = timed(t, name.bwd(), s, [&] { return launch_bwd_seq(dt, dk, dv, a, s); })) !=
       hipSuccess)
     return e;
   return timed(t, "k_grad", s, [&] { return launch_grad(dt, dk, dv, a, s); });
@@ -246,12 +266,13 @@ hipError_t launch_block_bwd_saved(int dk, int dv, const Args& a, const ConvArgs&
                                   const ConvArgs* cq, const ConvArgs* ck, hipStream_t s,
                                   Timing* t) {
   if (audit(Seq::BlockBwdSaved, a) >= 0) return hipErrorInvalidValue;
+  const Names name{use_chain(Dt::BF16, dk, a)};
   hipError_t e;
   // the chunk table serves packed input only; dense chunks are arithmetic
   if (a.cu && (e = timed(t, "k_chunk_table", s, [&] { return launch_chunk_table(a, s); })) !=
                   hipSuccess)
     return e;
-  if ((e = timed(t, "k_bwd_seq", s, [&] { return launch_bwd_seq(Dt::BF16, dk, dv, a, s); })) !=
+  if ((e = timed(t, name.bwd(), s, [&] { return launch_bwd_seq(Dt::BF16, dk, dv, a, s); })) !=
       hipSuccess)
     return e;
   if (cq && ck) {  // composed: the rule's dq, dk, then the prologue's backward of q and k

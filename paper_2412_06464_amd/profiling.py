@@ -10,9 +10,11 @@ counter record bench.py reads (profiles/traffic.json).
         --cmd ...   (the counter runs of MFMA_SETS)
 
 A kernel is identified by its key: base name and template arguments, e.g.
-k_prep<bf16,256,512,2,1> (the saving prep with the block prologue),
+k_prep<bf16,256,512,2,1,0> (the saving prep with the block prologue),
 k_fwd_seq<bf16,256,512,2>, k_grad<bf16,256,512,0>.  bench.py maps its timed
-launches to keys with kernel_key().
+launches to keys with kernel_key() and looks them up with find_kernel(): the
+chain passes come in several shapes, which a launch's name does not tell, so
+their keys end after the arguments that it does.
 
 Counters.  FETCH_SIZE and WRITE_SIZE (KiB per dispatch) are taken in runs of
 their own and scaled by what the same counter reads for a 1 GiB
@@ -97,12 +99,21 @@ def kernel_key(launch: str, dtype: str, dk: int, dv: int) -> str:
     t = "bf16" if dtype == "bf16" else "f32"
     blk = name.endswith("_block")
     base = name[:-len("_block")] if blk else name
-    if base in ("k_prep", "k_prep_save"):
-        mode = 2 if base == "k_prep_save" else (1 if call == "bwd" else 0)
-        return "k_prep<%s,%d,%d,%d,%d>" % (t, dk, dv, mode, int(blk))
-    modes = {"k_fwd_seq": 0, "k_fwd_seq_store": 1, "k_fwd_seq_save": 2}
-    if base in modes:
-        return "k_fwd_seq<%s,%d,%d,%d>" % (t, dk, dv, modes[base])
+    if base in ("k_prep", "k_prep_save", "k_prep_small", "k_prep_small_save"):
+        mode = 2 if base.endswith("_save") else (1 if call == "bwd" else 0)
+        small = "small" in base
+        if small and not blk:
+            return "k_prep_small<%d,%d>" % (dk, mode)
+        return "k_prep<%s,%d,%d,%d,%d,%d>" % (t, dk, dv, mode, int(blk), int(small))
+    modes = {"": 0, "_store": 1, "_save": 2}
+    m = re.match(r"k_fwd_(seq|chain)(_store|_save)?$", base)
+    if m:
+        mode = modes[m.group(2) or ""]
+        if m.group(1) == "chain":
+            return "k_fwd_chain<%d,%d,%d," % (dk, dv, mode)
+        return "k_fwd_seq<%s,%d,%d,%d>" % (t, dk, dv, mode)
+    if base == "k_bwd_chain":
+        return "k_bwd_chain<%d,%d," % (dk, dv)
     if base == "k_grad":
         return "k_grad<%s,%d,%d,%d>" % (t, dk, dv, int(blk))
     if base in ("k_bwd_seq", "k_recurrent"):
@@ -112,6 +123,15 @@ def kernel_key(launch: str, dtype: str, dk: int, dv: int) -> str:
     if name == "k_conv_bwd":  # the v prologue (no row norm): slices of 256 channels
         return "k_conv_bwd<%s,%d,%d>" % (t, dv, min(dv, 256))
     return name
+
+
+def find_kernel(kernels, key: str):
+    """The entry of ``kernels`` (by full kernel key) that a key of kernel_key()
+    names, or None."""
+    if not key.endswith(","):
+        return kernels.get(key)
+    found = [v for k, v in kernels.items() if k.startswith(key)]
+    return found[0] if len(found) == 1 else None
 
 
 def block_kernel_key(call: str, dk: int, dv: int) -> str:
