@@ -44,6 +44,11 @@
  *    `stream` (a hipStream_t; NULL = the default stream); outputs are valid
  *    when the stream reaches them.  Calls on different streams with distinct
  *    workspaces are independent.
+ *  - The same call on the same inputs gives the same bits.  In bfloat16 the
+ *    state passes come in two forms that round differently; which one runs
+ *    follows from the whole problem (how many sequence-heads it has side by
+ *    side), the same for every entry point.  So a sequence's bfloat16 results
+ *    can differ in rounding between calls whose B, H or boundaries differ.
  *  - Every argument check runs on the host before the first launch; a failed
  *    check returns its status and launches nothing.  A launch failure returns
  *    GDN_ERR_HIP.  No C++ exception crosses this boundary.
@@ -148,9 +153,10 @@ gdn_status gdn_chunk_bwd(const gdn_problem *p, const void *q, const void *k,
  * (device memory of gdn_chunk_saved_size bytes, owned by the caller, opaque
  * to it) with the per-chunk quantities the backward reads: the cumulative
  * log-gates, each chunk's entry state S_[t], the pseudo-values
- * V' = U~ - W~ S_[t] of the UT transform, and the chunk-local operands built
- * from q, k, beta and the gates (P, T = (I + A)^-1, W~, their transposes).
- * The layout of `saved` depends only on the problem; its content is valid
+ * V' = U~ - W~ S_[t] of the UT transform, and those chunk-local operands built
+ * from q, k, beta and the gates (P, T = (I + A)^-1, W~, their transposes) that
+ * the problem's form of the reverse pass reads; the rest of it is left as it
+ * was.  The layout of `saved` depends only on the problem; its content is valid
  * for the inputs the call was made with until the caller overwrites it.
  * `workspace` (gdn_chunk_fwd_save_workspace_size bytes) holds the call's
  * temporaries only and may be reused as soon as the call has run. */

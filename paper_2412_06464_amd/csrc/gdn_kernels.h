@@ -30,8 +30,9 @@ struct Args {
   // workspace: per-chunk operands of the sequential passes (dtype E), as MFMA
   // A operands in fragment order with the permuted contraction order.  The
   // passes of gdn_chain.h read q, k and v themselves: of these they use Wf
-  // (for T diag(b), 64 x 64), Pf, PTf and TTf only, and a fused forward that
-  // is not asked for the rule's q, k and v keeps them in Qf, KbT and Uc.
+  // (for T diag(b), 64 x 64), Pf, PTf and TTf only; Qf, KbT and Uc then hold the
+  // rule's q, k and v that a fused forward is not asked for, or copies of those
+  // that an output of the call would overwrite.
   void* Wf;   // W~ = T diag(b e^g) K      rows t, k = d     64 x dk
   void* KbT;  // Kbar^T                    rows d, k = t     dk x 64
   void* Uc;   // U~ = T diag(b) V          accumulator layout 64 x dv
