@@ -228,15 +228,17 @@ __device__ __forceinline__ void small_operands(const Args& a, size_t ch, f32x4 (
 // SMALL (with BLK only; k_prep_small is the one without): ahead of the passes
 // of gdn_chain.h, which read q, k and v themselves: beside the rule's q, k and
 // v only the 64 x 64 matrices are written (T diag(b) and P, and for the
-// backward P^T, T^T and Ak^T).  It lives by the phases' latency, like
-// k_prep_small, and takes that kernel's LDS plan (42, 45 and 55 KB at dk 64,
-// 128 and 256): three workgroups share a CU at dk <= 128 instead of the two of
-// the general plan, with which it held the plain fused forward back, us,
-// general prep and passes / two workgroups / three: 75.5 / 78.8 / 69.4
-// (48 x 1024, 128/128), 84.0 / 85.8 / 80.2 (64 x 1024), 71.9 / 73.0 / 67.7
-// (96 x 1024, 64/64), 1,324 / 1,218 / 1,073 (65,536 x 16 packed, 128/128).
+// backward P^T, T^T and Ak^T).
+// SHORT: at dk <= 128 it takes the LDS plan of k_prep_small (42 and 45 KB at dk
+// 64 and 128), and three workgroups share a CU instead of two; with two it held
+// the plain fused forward back, us, general prep and passes / two / three: 75.5 /
+// 78.8 / 69.4 (48 x 1024, 128/128), 84.0 / 85.8 / 80.2 (64 x 1024), 71.9 / 73.0 /
+// 67.7 (96 x 1024, 64/64), 1,324 / 1,218 / 1,073 (65,536 x 16 packed, 128/128).  At
+// dk = 256 that plan needs 55 KB, two workgroups as well, and is slower (prep
+// 288 -> 292 at 8 x 4096 x 6).
 template <class E, int DK, int DV, int MODE, bool BLK = false, bool SMALL = false>
 __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a) {
+  constexpr bool SHORT = SMALL && DK <= 128;
   static_assert(BLK || !SMALL, "k_prep_small");
   using M = Mfma<E>;
   // operands of the forward pass (diag(e^g) Q, P), of the reverse pass and
@@ -246,17 +248,17 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
   constexpr int LD = CH + PADE;  // rows of 64 elements
   constexpr int LDA = CH + 1;
   constexpr int NKC = CH / M::K;
-  // SMALL: T and the products of the block recursion lie over the slices, the
+  // SHORT: T and the products of the block recursion lie over the slices, the
   // prologue's weights have their place
   constexpr int STAGE = 2 * CH * LD * (int)sizeof(E), INV = (CH * LDA + 32 * 33) * 4;
-  __shared__ __align__(16) unsigned char sXY[SMALL && INV > STAGE ? INV : STAGE];
-  __shared__ __align__(16) E sT[SMALL ? 1 : CH * LD];  // T, row-major
-  __shared__ __align__(16) E sP[SMALL ? 1 : CH * LD];  // P, row-major
+  __shared__ __align__(16) unsigned char sXY[SHORT && INV > STAGE ? INV : STAGE];
+  __shared__ __align__(16) E sT[SHORT ? 1 : CH * LD];  // T, row-major
+  __shared__ __align__(16) E sP[SHORT ? 1 : CH * LD];  // P, row-major
   __shared__ float sA[CH * LDA];                       // diag(b) A
-  __shared__ __align__(16) float sInv[SMALL ? 4 * (2 * DK + DV) : CH * LDA + 32 * 33];
+  __shared__ __align__(16) float sInv[SHORT ? 4 * (2 * DK + DV) : CH * LDA + 32 * 33];
   E* sX = (E*)sXY;       // K slice (Gram), then K_s^T or (b V_s)^T
   E* sY = sX + CH * LD;  // Q slice (Gram), then Q_s^T (backward)
-  float* sTf = SMALL ? (float*)sXY : sInv;  // T in fp32
+  float* sTf = SHORT ? (float*)sXY : sInv;  // T in fp32
   float* sYb = sTf + CH * LDA;              // products of the block recursion
   __shared__ float sg[CH], sb[CH], seg[CH], sdec[CH], sbeg[CH];
 
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
                   "staging and row sums must fit in A");
     E* sXs = reinterpret_cast<E*>(sA);                    // staged slice (A is not formed yet)
     float* sNrm = sA + (S::BYTES + 15) / 16 * 4;          // [4 waves][CH] row sums
-    // weights by lag of the q | k | v channels, where T is formed later (SMALL:
+    // weights by lag of the q | k | v channels, where T is formed later (SHORT:
     // the slices' place is taken until then)
     float4* sWl = reinterpret_cast<float4*>(sInv);
     static_assert((2 * DK + DV) * sizeof(float4) <= sizeof(sInv), "weights must fit");
@@ -347,15 +349,14 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
     pro_weights(sWl + 2 * DK, a.cwv + (size_t)h * DV * a.cw, a.cw, DV, tid, 256);
     const int nprev = start > pro_seq_start(a, ci) ? 3 : 0;  // chunks start 64-aligned in a sequence
     // the chunk's rows of all three projections into L2 first, where the
-    // workgroups an XCD runs at once (two per CU, three with SMALL at dk <=
-    // 128, 32 CUs) keep theirs within its 4 MB L2: 64 x 67 rows x (2 dk + dv) x 2
+    // workgroups an XCD runs at once (two per CU, three with SHORT, 32 CUs) keep theirs within its 4 MB L2: 64 x 67 rows x (2 dk + dv) x 2
     // bytes is 3.3 MB at 128/128 (prep 1.29 -> 1.20 ms at 65,536 tokens x 16
     // heads) but 8.8 MB at 256/512, where the warmed lines are gone before they
     // are read (0.54 -> 0.57 ms); 96 x is 4.9 MB at 128/128 (prep 39.2 us with
     // the warm-up and 35.5 without at 48 x 1024, 663 and 671 at 65,536 tokens x
     // 16 heads).  Their offsets from the first staged row fit 32 bits.
     __shared__ float sWarm[64];
-    constexpr int WGS = 32 * (SMALL && DK <= 128 ? 3 : 2);
+    constexpr int WGS = 32 * (SHORT ? 3 : 2);
     constexpr bool WARM = WGS * (CH + 3) * (2 * DK + DV) * (int)sizeof(E) <= (4 << 20);
     if (WARM && (size_t)(CH + 3) * H * DV * sizeof(E) < (1u << 31)) {
       pro_warm((const E*)a.xq, DK, H, h, start, len, nprev, sWarm, tid, 256);
@@ -491,8 +492,8 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
       if (a.yq) rows_out(sY, a.yq, DK, 64 * s);
     }
     wave_mma_nt<E, 1, 4, 64>(kk, sX + w * 16 * LD, LD, sX, LD);
-    if (BOUT || !SMALL) wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
-    if constexpr (SMALL) wave_mma_nt<E, 1, 4, 64>(kq, sX + w * 16 * LD, LD, sY, LD);
+    if (BOUT || !SHORT) wave_mma_nt<E, 1, 4, 64>(qk, sY + w * 16 * LD, LD, sX, LD);
+    if constexpr (SHORT) wave_mma_nt<E, 1, 4, 64>(kq, sX + w * 16 * LD, LD, sY, LD);
     if (FOUT && !SMALL) {
       // diag(e^g) Q as A operands (rows t, k = d) for the output of the forward pass
       export_afrag_perm_kslice<E, CH, DK, 64, 256>(
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
     }
     lds_barrier();
   });
-  if constexpr (SMALL) {
+  if constexpr (SHORT) {
     small_operands<MODE>(a, ch, kk, qk, kq, sg, sb, sA, sTf, sYb);
     return;
   }
@@ -534,11 +535,19 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
   invert_unit_lower<LDA>(sA, sTf, sYb);
   // T (zero above the diagonal blocks, where the buffer holds none)
   auto T_at = [&](int r, int i) { return ((i >> 4) > (r >> 4)) ? 0.f : sTf[r * LDA + i]; };
-  for (int idx = tid; idx < CH * CH; idx += 256) {
-    const int r = idx >> 6, i = idx & 63;
-    sT[r * LD + i] = to_e<E>(T_at(r, i));
+  if constexpr (SMALL) {
+    export_afrag_perm<E, CH, CH, 256>((E*)a.Wf + ch * CH * CH,
+                                      [&](int t, int i) { return T_at(t, i) * sb[i]; });
+    if (BOUT)
+      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                        [&](int i, int t) { return T_at(t, i); });
+  } else {
+    for (int idx = tid; idx < CH * CH; idx += 256) {
+      const int r = idx >> 6, i = idx & 63;
+      sT[r * LD + i] = to_e<E>(T_at(r, i));
+    }
+    lds_barrier();
   }
-  lds_barrier();
 
   // ---- 64 x 64 operands
   if (FOUT) {
@@ -548,9 +557,11 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
   if (BOUT) {
     export_afrag_perm<E, CH, CH, 256>((E*)a.PTf + ch * CH * CH,
                                       [&](int i, int t) { return to_f(sP[t * LD + i]); });
-    export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
-                                      [&](int i, int t) { return to_f(sT[t * LD + i]); });
+    if (!SMALL)
+      export_afrag_perm<E, CH, CH, 256>((E*)a.TTf + ch * CH * CH,
+                                        [&](int i, int t) { return to_f(sT[t * LD + i]); });
   }
+  if constexpr (SMALL) return;
 
   // ---- dk slices: W~ (and -W~^T), Kbar^T, (e^g Q)^T
   static_for<0, SMALL ? 0 : KS>([&](auto sc) {
