@@ -640,10 +640,11 @@ __global__ __launch_bounds__(256, SMALL && DK <= 128 ? 3 : 2) void k_prep(Args a
 // the bound of three only keeps from spilling): the inverse lies where the staged
 // slices were, P and its transpose go out straight from accumulators (P from
 // K Q^T), and rows are loaded eight lanes to 128 bytes, not one lane to a row.
-// Against k_prep (two workgroups a CU, a lane to a row), bf16, warm, us: forward
-// 96 -> 55 (8 x 4096 x 6 heads, 256/512; 245 MB, 4.5 TB/s), 41 -> 30 (4 x 2048
-// x 16, 128/128), 132 -> 80 (8 x 4096 x 16, 64/64); saving pass 105 -> 82 (the
-// first), 415 -> 370 (65,536 x 16, 128/128, packed; 1.19 GB, 3.2 TB/s).
+// Against k_prep (two workgroups a CU, a lane to a row), bf16, warm, us (bytes by
+// counters): forward 96 -> 53 (8 x 4096 x 6 heads, 256/512; 271 MB, 5.1 TB/s),
+// 41 -> 30 (4 x 2048 x 16, 128/128; 113 MB, 3.8 TB/s), 132 -> 80 (8 x 4096 x 16,
+// 64/64); saving pass 105 -> 84 (the first; 380 MB, 4.5 TB/s), 415 -> 337 (65,536 x
+// 16, 128/128, packed; 1.61 GB, 4.8 TB/s).
 template <int DK, int MODE>
 __global__ __launch_bounds__(256, DK > 128 ? 3 : 4) void k_prep_small(Args a) {
   using E = bf16;
